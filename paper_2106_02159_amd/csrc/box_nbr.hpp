@@ -30,7 +30,43 @@ struct BoxGeom {
   int32_t nn;
   int32_t n[3];  // nodes per direction (n[2] = 1 in 2D)
   int32_t per;   // bit d set: direction d is periodic
+  // Entries of interior rows (all neighbours present, no periodic seam
+  // between), by class: bit d set where the offset along d is not 0.  m_ij;
+  // |c_ij . e| along e (0 where the offset along e is 0; the sign is the
+  // offset's); |c_ij|; c_ij / |c_ij| without the signs.
+  double im[8], ic[8][3], icn[8], inrm[8][3];
 };
+
+// Class of slot k in the interior-entry tables.
+template <int DIM>
+__host__ __device__ constexpr int slot_class(int k) {
+  return (k % 3 != 1 ? 1 : 0) | ((k / 3) % 3 != 1 ? 2 : 0) |
+         (DIM == 3 && k / 9 != 1 ? 4 : 0);
+}
+
+// The interior-entry tables of a mesh from its 1D mass factors; the products
+// are formed as BoxNbr forms them, so m_ij and c_ij are the same values.
+template <int DIM>
+inline void fill_interior(BoxGeom *g) {
+  for (int c = 0; c < 8; ++c) {
+    double f[3] = {1.0, 1.0, 1.0}, m = 1.0, c2 = 0.0;
+    for (int d = 0; d < DIM; ++d) {
+      f[d] = (c >> d) & 1 ? g->m_off[d] : g->m_inner[d];
+      m *= f[d];
+    }
+    g->im[c] = m;
+    for (int e = 0; e < 3; ++e) {
+      double v = e < DIM && ((c >> e) & 1) ? 0.5 : 0.0;
+      for (int d = 0; d < DIM; ++d)
+        if (d != e) v *= f[d];
+      g->ic[c][e] = v;
+      c2 += v * v;
+    }
+    const double cn = __builtin_sqrt(c2);
+    g->icn[c] = cn;
+    for (int e = 0; e < 3; ++e) g->inrm[c][e] = cn > 0.0 ? g->ic[c][e] / cn : 0.0;
+  }
+}
 
 // Reads of the mesh geometry.  On the device they go through the constant
 // address space: the geometry is never written by a kernel, and its
@@ -119,6 +155,11 @@ struct BoxNbr {
   // registers in 3D).  Emits no instruction.
   __device__ __forceinline__ void fence() {
     asm volatile("" : "+v"(i), "+v"(ends), "+v"(bad));
+  }
+
+  // All 3^DIM neighbours exist and none lies across a periodic seam.
+  __host__ __device__ __forceinline__ bool interior() const {
+    return ends == 0 && !isolated();
   }
 
   // An isolated row has both ends along x set in `bad`, which no mesh node

@@ -71,13 +71,13 @@ template <int SEV>
 __device__ __forceinline__ double lambda_max(const Gas &g, double uL, double pL,
                                              double aL, double bL, double uR,
                                              double pR, double aR, double bR) {
-  const double num = aL + aR - 0.5 * g.gm1 * (uR - uL);
+#pragma clang fp contract(off)  // the same bits in every kernel
+  const double num = fma(-0.5 * g.gm1, uR - uL, aL + aR);
   double ptr = 0.0;
   if (num > 0.0) ptr = pow_inv_ex<SEV>(g, num * fast_rcp(bL + bR));
-  const double l1 =
-      uL - aL * fast_sqrt(1.0 + g.cg * fmax(ptr * fast_rcp(pL) - 1.0, 0.0));
-  const double l3 =
-      uR + aR * fast_sqrt(1.0 + g.cg * fmax(ptr * fast_rcp(pR) - 1.0, 0.0));
+  const double sL = fast_sqrt(fma(g.cg, fmax(fma(ptr, fast_rcp(pL), -1.0), 0.0), 1.0));
+  const double sR = fast_sqrt(fma(g.cg, fmax(fma(ptr, fast_rcp(pR), -1.0), 0.0), 1.0));
+  const double l1 = fma(-aL, sL, uL), l3 = fma(aR, sR, uR);
   return fmax(fmax(-l1, 0.0), fmax(l3, 0.0));
 }
 

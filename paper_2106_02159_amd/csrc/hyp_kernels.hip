@@ -2,6 +2,8 @@
 // See hyp_kernels.hpp for the sweep structure and data layout.
 #include "hyp_kernels.hpp"
 
+#include "line_sweep.hpp"
+
 #include <algorithm>
 #include <climits>
 #include <type_traits>
@@ -10,21 +12,20 @@ namespace ns {
 
 namespace {
 
-enum { AP_OFF = 0 };  // aux layout: v[0..DIM-1], p, a, b, eta, Phi
-
+// aux layout: (a, b) side by side per node, then eta, Phi
 template <int DIM> struct Aux {
-  static constexpr int P = DIM, A = DIM + 1, B = DIM + 2, ETA = DIM + 3,
-                       PHI = DIM + 4, COUNT = DIM + 5;
+  static constexpr int AB = 0, ETA = 2, PHI = 3, COUNT = 4;
 };
+// a and b = a p^(-(gamma-1)/(2 gamma)) of node i
+__device__ __forceinline__ double2 aux_ab(const double *__restrict__ aux, int64_t i) {
+  return *reinterpret_cast<const double2 *>(aux + 2 * i);
+}
 
 // Row width 3^DIM, processed in unrolled chunks of CH slots: the neighbour
 // gathers of a chunk are issued together, while the chunk size bounds the
 // registers a lane holds (and so the occupancy that hides gather latency).
 #ifndef NS_CH_VISC
 #define NS_CH_VISC 1
-#endif
-#ifndef NS_CH_LO
-#define NS_CH_LO 1
 #endif
 #ifndef NS_CH_LIM1
 #define NS_CH_LIM1 1
@@ -63,6 +64,16 @@ __device__ __forceinline__ int64_t eidx(int k, int64_t i) {
 #ifndef NS_NT
 #define NS_NT 2
 #endif
+template <typename T>
+__device__ __forceinline__ T ld_once(global_ptr<const T> p) {
+  if constexpr (NS_NT >= 1) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <typename T>
+__device__ __forceinline__ void st_once(global_ptr<T> p, T v) {
+  if constexpr (NS_NT >= 2) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
 template <typename T>
 __device__ __forceinline__ T ld_once(const T *p) {
   if constexpr (NS_NT >= 1) return __builtin_nontemporal_load(p);
@@ -147,19 +158,95 @@ __device__ __forceinline__ void store_state(T *__restrict__ U, int64_t N, int64_
   if constexpr (NC & 1) U[(NC - 1) * N + i] = u[NC - 1];
 }
 
-// f(u) c = (rho v.c, m (v.c) + p c, (v.c)(E + p)) from primitives v, p.
-template <int DIM>
-__device__ __forceinline__ void flux_dot(const double *u, const double *v,
-                                         double p, const double *c,
-                                         double *fc) {
-  double vc = 0.0;
+// A line of a node vector (line_sweep.hpp): rows b + off.
+template <int NC, typename T>
+__device__ __forceinline__ void line_state(const T *__restrict__ U, int64_t N, int64_t b,
+                                           uint32_t off, double *u) {
+  using T2 = vec2<T>;
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) vc += v[k] * c[k];
-  fc[0] = u[0] * vc;
-#pragma unroll
-  for (int k = 0; k < DIM; ++k) fc[1 + k] = u[1 + k] * vc + p * c[k];
-  fc[DIM + 1] = vc * (u[DIM + 1] + p);
+  for (int p = 0; p < NC / 2; ++p) {
+    const T2 v = line_ld(reinterpret_cast<const T2 *>(U + 2 * p * N), b, off);
+    u[2 * p] = v.x;
+    u[2 * p + 1] = v.y;
+  }
+  if constexpr (NC & 1) u[NC - 1] = line_ld(U + (NC - 1) * N, b, off);
 }
+
+// The value of the neighbour at dx = -1 or +1 from the line's values.
+__device__ __forceinline__ double side(int dx, double end, double x) {
+  return dx < 0 ? from_left(end, x) : from_right(end, x);
+}
+
+// Does the line path handle row i?  (Interior rows; the others are listed.)
+template <typename LT>
+__device__ __forceinline__ bool line_row(const DevGraphT<LT> &G, int64_t i) {
+  return (G.spec[min(i, G.N - 1)] == 0) & (i < G.N);
+}
+
+template <typename LT>
+__device__ __forceinline__ const BoxGeom *block_geo(const DevGraphT<LT> &G, uint32_t blk) {
+  return &G.geo[G.seg ? geo_ld(&G.seg[blk]) : 0];
+}
+
+// Entry of slot k of a row of the block that starts at row r0 (a multiple
+// of 64), e0 = the lane's entry of slot 0 within the block; and the entry of
+// slot k of row jb + tid (jb >= 0 for every active lane's row).
+template <int DIM, typename T>
+__device__ __forceinline__ global_ptr<T> edge_at(T *a, int64_t r0, int k, uint32_t e0) {
+  constexpr int W = DIM == 2 ? 9 : 27;
+  return lane_at(a + r0 * W + k * 64, e0);
+}
+template <int DIM, typename T>
+__device__ __forceinline__ global_ptr<T> edge_t(T *a, int64_t jb, int k, uint32_t tid) {
+  constexpr int W = DIM == 2 ? 9 : 27;
+  // rows counted from the slice boundary below jb
+  const uint32_t t = (uint32_t)(jb & 63) + tid;
+  const uint32_t e = (t >> 6) * (W * 64) + (t & 63);
+  return lane_at(a + (jb >> 6) * (W * 64) + k * 64, e);
+}
+
+// Blocks [0, spec_blocks) of a line sweep take the listed rows, the others row
+// block blockIdx.x - spec_blocks.  A listed row is shared by the lanes of a
+// wave, one per stencil line: on small meshes, where one wave per SIMD hides
+// nothing, its 3^d entries one after another took longer than all the rest
+// of the launch.
+template <int DIM, typename LT>
+__host__ __device__ __forceinline__ uint32_t spec_blocks(const DevGraphT<LT> &G) {
+  constexpr uint32_t per = (64 / (DIM == 2 ? 3 : 9)) * (kBlock / 64);
+  return ((uint32_t)G.nsrow + per - 1) / per;
+}
+template <int DIM>
+struct SpecLane {
+  static constexpr int NL = DIM == 2 ? 3 : 9, ROWS = 64 / NL;
+  int64_t i;  // row
+  int line;   // this lane's line
+  int base;   // first lane of the row
+  bool ok;    // (lanes without a row repeat another one's, without stores)
+  template <typename LT>
+  __device__ __forceinline__ explicit SpecLane(const DevGraphT<LT> &G) {
+    const int lane = threadIdx.x & 63, grp = lane / NL;
+    line = lane - grp * NL;
+    base = grp * NL;
+    const int t = (int)(blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * ROWS + grp;
+    ok = grp < ROWS && t < G.nsrow;
+    i = G.srow[min(t, G.nsrow - 1)];
+  }
+  // Sum and minimum over the row's lines, in line order.
+  __device__ __forceinline__ double sum(double x) const {
+    double s = 0.0;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) s += __shfl(x, min(base + l, 63));
+    line_keep(s);
+    __builtin_amdgcn_sched_barrier(0);  // (one value at a time: registers)
+    return s;
+  }
+  __device__ __forceinline__ double least(double x) const {
+    double s = x;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) s = fmin(s, __shfl(x, min(base + l, 63)));
+    return s;
+  }
+};
 
 __device__ __forceinline__ double block_min(double v) {
   __shared__ double red[kBlock / 64];
@@ -174,17 +261,17 @@ __device__ __forceinline__ double block_min(double v) {
   return v;
 }
 
-// Velocity and pressure of a conserved state.  k_prim stores them per node
-// for k_visc without the indicator; the sweeps that gather a neighbour's
-// whole state anyway compute them with this same function instead.
+// Velocity and pressure of a conserved state; returns the internal energy
+// per volume.  The sweeps read whole states and compute them from there.
 template <int DIM>
 __device__ __forceinline__ double vel_pres(const Gas &g, const double *u, double *v,
                                            double &p) {
+#pragma clang fp contract(off)  // the same bits in every kernel
   const double ir = fast_rcp(u[0]);
-  double m2 = 0.0;
+  double m2 = u[1] * u[1];
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) m2 += u[1 + k] * u[1 + k];
-  const double eps = u[DIM + 1] - 0.5 * m2 * ir;  // rho e
+  for (int k = 1; k < DIM; ++k) m2 = fma(u[1 + k], u[1 + k], m2);
+  const double eps = fma(-0.5 * m2, ir, u[DIM + 1]);  // rho e
   p = g.gm1 * eps;
 #pragma unroll
   for (int k = 0; k < DIM; ++k) v[k] = u[1 + k] * ir;
@@ -192,12 +279,11 @@ __device__ __forceinline__ double vel_pres(const Gas &g, const double *u, double
 }
 
 // ---------------------------------------------------------------------------
-// VP: also store v and p (read only by k_visc without the indicator; the
-// other sweeps compute them from the states they gather).
-template <int DIM, bool VP>
+template <int DIM>
 __device__ __forceinline__ void prim_row(int64_t N, const double *__restrict__ U,
                                          double *__restrict__ aux, const Gas &g,
                                          int64_t i) {
+#pragma clang fp contract(off)  // the same bits in every kernel
   if (i >= N) return;
   using X = Aux<DIM>;
   double u[DIM + 2], v[DIM], p;
@@ -209,156 +295,329 @@ __device__ __forceinline__ void prim_row(int64_t N, const double *__restrict__ U
   // entropy and p^(-(gamma-1)/(2 gamma)) = exp(-ex log p)
   const double le = log(eps);
   const double s = le - g.gamma * log(r);
-  if constexpr (VP) {
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) aux[k * N + i] = v[k];
-    aux[X::P * N + i] = p;
-  }
-  aux[X::A * N + i] = a;
-  aux[X::B * N + i] = a * exp(-g.ex * (g.lgm1 + le));
+  double2 ab;
+  ab.x = a;
+  ab.y = a * exp(-g.ex * (g.lgm1 + le));
+  *reinterpret_cast<double2 *>(aux + 2 * i) = ab;
   aux[X::ETA * N + i] = -r * s;
   aux[X::PHI * N + i] = exp(s);
 }
 
-template <int DIM, bool VP>
+template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_prim(int64_t N,
                                                  const double *__restrict__ U,
                                                  double *__restrict__ aux,
                                                  Gas g) {
-  prim_row<DIM, VP>(N, U, aux, g, plain_id());
+  prim_row<DIM>(N, U, aux, g, plain_id());
 }
 
 // ---------------------------------------------------------------------------
 // Graph viscosity d^L_ij (j > i, stored at (i,j) and (j,i)) and alpha_i.
-// The column indices of the row follow from its place in the box mesh; each
-// chunk of slots gathers its neighbour data unconditionally (absent entries
-// read row i itself) so that the loads of a chunk are in flight together, and the
-// arithmetic is predicated on the entry being present.
+//
+// An interior row and the same row met by the general path (the persistent
+// steps) must give the same bits, so the arithmetic of an entry is written
+// once, here, with its fused multiply-adds spelled out.  MASK: the
+// components of c_ij that can be nonzero (a zero component adds exact
+// zeros, so leaving it out changes nothing).
+template <int DIM, int MASK>
+__device__ __forceinline__ double dot_c(const double *v, const double *c) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  double s = 0.0;
+  bool first = true;
+#pragma unroll
+  for (int q = 0; q < DIM; ++q) {
+    if (!((MASK >> q) & 1)) continue;
+    s = first ? v[q] * c[q] : fma(v[q], c[q], s);
+    first = false;
+  }
+  return s;
+}
+
+// f(u) c = (rho v.c, m (v.c) + p c, (v.c)(E + p)); vc = v.c
+template <int DIM, int MASK>
+__device__ __forceinline__ void flux_c(const double *u, double vc, double p, const double *c,
+                                       double *fc) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  fc[0] = u[0] * vc;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k)
+    fc[1 + k] = (MASK >> k) & 1 ? fma(u[1 + k], vc, p * c[k]) : u[1 + k] * vc;
+  fc[DIM + 1] = vc * (u[DIM + 1] + p);
+}
+
+// Entropy variables eta'(U_i) of a row: what its commutator terms need.
+template <int DIM>
+__device__ __forceinline__ void entropy_vars(const Gas &g, const double *ui, double eps,
+                                             double eta, double *etap) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  double m2 = ui[1] * ui[1];
+#pragma unroll
+  for (int k = 1; k < DIM; ++k) m2 = fma(ui[1 + k], ui[1 + k], m2);
+  const double s = -eta / ui[0];
+  const double ie = 1.0 / eps;
+  etap[0] = g.gamma - s - m2 / (2.0 * ui[0] * eps);
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) etap[1 + k] = ui[1 + k] * ie;
+  etap[DIM + 1] = -ui[0] * ie;
+}
+
+// Adds entry (i,j) to the indicator's sums N_i, D_i, S_i.
+template <int DIM, int MASK>
+__device__ __forceinline__ void indicator_term(const double *etap, const double *uj,
+                                               const double *vj, double pj, double aj,
+                                               double etaj, const double *c, double cn,
+                                               double &num, double &den, double &scl) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  const double vc = dot_c<DIM, MASK>(vj, c);
+  double fc[DIM + 2];
+  flux_c<DIM, MASK>(uj, vc, pj, c, fc);
+  double t = etaj * vc;
+#pragma unroll
+  for (int q = 0; q < DIM + 2; ++q) t = fma(-etap[q], fc[q], t);
+  num += t;
+  den += fabs(t);
+  scl = fma(cn * aj, uj[0] + fabs(etaj), scl);
+}
+
+// The general path of a row: any boundary, any place.  Row data, and the
+// entries of one stencil line (each slot's neighbour gathered on its own;
+// absent entries read row i itself, with c = 0).
+template <int DIM, int IND>
+struct ViscRow {
+  static constexpr int NC = DIM + 2;
+  double vi[DIM], pi, ai, bi, etap[NC];
+  bool wall;
+  template <typename LT>
+  __device__ __forceinline__ ViscRow(const DevGraphT<LT> &G, const double *__restrict__ U,
+                                     const double *__restrict__ aux, const Gas &g, int64_t i) {
+    double ui[NC];
+    load_state<NC>(U, G.N, i, ui);
+    const double2 ab = aux_ab(aux, i);
+    ai = ab.x;
+    bi = ab.y;
+    wall = G.wall[i] != 0;
+    const double eps = vel_pres<DIM>(g, ui, vi, pi);
+    if constexpr (IND == 0) entropy_vars<DIM>(g, ui, eps, aux[Aux<DIM>::ETA * G.N + i], etap);
+  }
+};
+
+// Adds the entries of line l to the indicator's sums and stores d_ij for
+// j > i.  ANY: the row may be interior (its coefficients are then the
+// table's).
+template <int DIM, int IND, int SEV, bool ANY, typename LT>
+__device__ __forceinline__ void visc_line(const DevGraphT<LT> &G,
+                                          const double *__restrict__ U,
+                                          const double *__restrict__ aux,
+                                          LT *__restrict__ d, const Gas &g,
+                                          const BoxNbr<DIM> &jv, int64_t i,
+                                          const ViscRow<DIM, IND> &R, int l, bool store,
+                                          double &num, double &den, double &scl) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  constexpr int NC = DIM + 2, ALL = (1 << DIM) - 1, C = Cfg<DIM>::W / 2;
+  const int64_t N = G.N;
+  const bool in = ANY && jv.interior();
+#pragma unroll 1
+  for (int t = 0; t < 3; ++t) {
+    const int k = 3 * l + t;
+    const int32_t j = jv[k];
+    const int64_t js = j >= 0 ? j : i;
+    double uj[NC];
+    load_state<NC>(U, N, js, uj);
+    const double2 abj = aux_ab(aux, js);
+    const double aj = abj.x, bj = abj.y;
+    const double etaj = IND == 0 ? aux[Aux<DIM>::ETA * N + js] : 0.0;
+    double c[DIM], vj[DIM], pj;
+    jv.grad(k, c);
+#pragma unroll
+    for (int q = 0; q < DIM; ++q) c[q] = j >= 0 ? c[q] : 0.0;
+    vel_pres<DIM>(g, uj, vj, pj);
+    const int cls = slot_class<DIM>(k);
+    double c2 = c[0] * c[0];
+#pragma unroll
+    for (int q = 1; q < DIM; ++q) c2 = fma(c[q], c[q], c2);
+    double cn = fast_sqrt(c2);
+    if (in) cn = jv.g->icn[cls];
+    if constexpr (IND == 0)
+      indicator_term<DIM, ALL>(R.etap, uj, vj, pj, aj, etaj, c, cn, num, den, scl);
+    if (k != C && j > i) {
+      double n[DIM];
+      const double icn = fast_rcp(cn);
+#pragma unroll
+      for (int q = 0; q < DIM; ++q) {
+        n[q] = c[q] * icn;
+        if (in) n[q] = copysign(jv.g->inrm[cls][q], c[q]);
+      }
+      const double uL = dot_c<DIM, ALL>(R.vi, n), uR = dot_c<DIM, ALL>(vj, n);
+      double dij = lambda_max<SEV>(g, uL, R.pi, R.ai, R.bi, uR, pj, aj, bj) * cn;
+      if (R.wall) {
+        // both ends may be on the wall: c_ji != -c_ij, take both directions
+        double ct[DIM];
+        grad_transposed<DIM>(k, c, ct);
+        double ct2 = ct[0] * ct[0];
+#pragma unroll
+        for (int q = 1; q < DIM; ++q) ct2 = fma(ct[q], ct[q], ct2);
+        const double ctn = fast_sqrt(ct2);
+        const double ictn = fast_rcp(ctn);
+#pragma unroll
+        for (int q = 0; q < DIM; ++q) ct[q] *= ictn;
+        dij = fmax(dij, lambda_max<SEV>(g, dot_c<DIM, ALL>(vj, ct), pj, aj, bj,
+                                        dot_c<DIM, ALL>(R.vi, ct), R.pi, R.ai, R.bi) * ctn);
+      }
+      if (store) {
+        const LT dst = to_lt_up<LT>(dij);
+        st_once(&d[eidx<DIM>(k, i)], dst);
+        st_once(&d[eidx<DIM>(tslot<DIM>(k), j)], dst);
+      }
+    }
+  }
+}
+
+// alpha_i from its sums (an isolated node -- a padding row of a pack -- has
+// den = scl = 0).
+template <int IND, typename LT>
+__device__ __forceinline__ LT alpha_of(double num, double den, double scl) {
+  if constexpr (IND == 0)
+    return to_lt<LT>(den + scl > 0.0 ? fabs(num) / fma(1e-2, scl, den) : 0.0);
+  return LT(IND == 1 ? 1 : 0);
+}
+
+// A listed row, shared by the lanes of its lines.
 template <int DIM, int IND, int SEV, typename LT>
+__device__ __forceinline__ void visc_spec(const DevGraphT<LT> &G,
+                                          const double *__restrict__ U,
+                                          const double *__restrict__ aux,
+                                          LT *__restrict__ d, LT *__restrict__ alpha,
+                                          const Gas &g) {
+  const SpecLane<DIM> L(G);
+  const ViscRow<DIM, IND> R(G, U, aux, g, L.i);
+  double num = 0.0, den = 0.0, scl = 0.0;
+  visc_line<DIM, IND, SEV, false, LT>(G, U, aux, d, g, row_nbr<DIM>(G, L.i), L.i, R, L.line,
+                                      L.ok, num, den, scl);
+  num = L.sum(num);
+  den = L.sum(den);
+  scl = L.sum(scl);
+  if (L.ok && L.line == 0) alpha[L.i] = alpha_of<IND, LT>(num, den, scl);
+}
+
+// Any row by one lane (the persistent steps): sums along the row as the line
+// sweep forms them if it is interior, line by line as visc_spec if not.
+template <int DIM, int SEV, typename LT>
 __device__ __forceinline__ void visc_row(const DevGraphT<LT> &G,
                                          const double *__restrict__ U,
                                          const double *__restrict__ aux,
                                          LT *__restrict__ d, LT *__restrict__ alpha,
-                                         const Gas &g, uint32_t blk, int64_t i) {
-  using X = Aux<DIM>;
-  using C = Cfg<DIM, NS_CH_VISC>;
-  constexpr int NC = C::NC;
-  const int64_t N = G.N;
-  if (i >= N) return;
-  BoxNbr<DIM> jv = block_nbr<DIM>(G, blk, i);
-  double vi[DIM], pi;
-  const double ai = aux[X::A * N + i], bi = aux[X::B * N + i];
-  const bool wall_i = G.wall[i] != 0;
-  double etap[NC];
-  if constexpr (IND == 0) {
-    double ui[NC];
-    load_state<NC>(U, N, i, ui);
-    const double eps = vel_pres<DIM>(g, ui, vi, pi);  // rho e
-    const double ri = ui[0];
-    double m2 = 0.0;
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-      m2 += ui[1 + k] * ui[1 + k];
-      etap[1 + k] = ui[1 + k];
+                                         const Gas &g, BoxNbr<DIM> jv, int64_t i) {
+  const ViscRow<DIM, 0> R(G, U, aux, g, i);
+  const bool in = jv.interior();
+  double num = 0.0, den = 0.0, scl = 0.0, tn = 0.0, td = 0.0, ts = 0.0;
+#pragma unroll 1
+  for (int l = 0; l < Cfg<DIM>::W / 3; ++l) {
+    visc_line<DIM, 0, SEV, true, LT>(G, U, aux, d, g, jv, i, R, l, true, num, den, scl);
+    if (!in) {
+      tn += num; td += den; ts += scl;
+      num = den = scl = 0.0;
     }
-    const double s = -aux[X::ETA * N + i] / ri;
-    const double ie = 1.0 / eps;
-    etap[0] = g.gamma - s - m2 / (2.0 * ri * eps);
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) etap[1 + k] *= ie;
-    etap[NC - 1] = -ri * ie;
-  } else {
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) vi[k] = aux[k * N + i];
-    pi = aux[X::P * N + i];
   }
+  alpha[i] = in ? alpha_of<0, LT>(num, den, scl) : alpha_of<0, LT>(tn, td, ts);
+}
+
+// The interior rows of row block blk, line by line (line_sweep.hpp).
+template <int DIM, int IND, int SEV, typename LT>
+__device__ __forceinline__ void visc_lines(const DevGraphT<LT> &G,
+                                           const double *__restrict__ U,
+                                           const double *__restrict__ aux,
+                                           LT *__restrict__ d, LT *__restrict__ alpha,
+                                           const Gas &g, uint32_t blk) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  using X = Aux<DIM>;
+  constexpr int NC = DIM + 2, W = Cfg<DIM>::W;
+  const int64_t N = G.N, r0 = (int64_t)blk * kBlock;
+  uint32_t tid = threadIdx.x;
+  const uint32_t lane = tid & 63;
+  const BoxGeom *geo = block_geo(G, blk);
+  const int64_t n0 = geo_ld(&geo->n[0]), n01 = n0 * geo_ld(&geo->n[1]);
+  const bool act = line_row(G, r0 + tid);
+  const bool edge = ((lane + 1) & 63) < 2;  // lanes 63 and 0
+  const Line own = make_line(r0, 0, N, tid);
+  double ui[NC], vi[DIM], pi, etap[NC];
+  line_state<NC>(U, N, own.b, own.c, ui);
+  const vec2<double> abi = line_ld(reinterpret_cast<const vec2<double> *>(aux), own.b, own.c);
+  const double etai = IND == 0 ? line_ld(aux + X::ETA * N, own.b, own.c) : 0.0;
+  {
+    const double eps = vel_pres<DIM>(g, ui, vi, pi);
+    if constexpr (IND == 0) entropy_vars<DIM>(g, ui, eps, etai, etap);
+  }
+  // this lane's entry of slot 0 relative to the block's first edge entry
+  const uint32_t e0 = (tid >> 6) * (W * 64) + lane;
   double num = 0.0, den = 0.0, scl = 0.0;
+  static_for<0, W / 3>([&](auto line) __attribute__((always_inline)) {
+    constexpr int ln = decltype(line)::value;
+    constexpr int dy = ln % 3 - 1, dz = DIM == 3 ? ln / 3 - 1 : 0;
+    constexpr bool self = dy == 0 && dz == 0;
+    // without the indicator only the entries with j > i
+    if constexpr (IND != 0 && 3 * ln + 2 <= W / 2) return;
+    const int64_t delta = dy * n0 + dz * n01;
+    line_fence(tid);
+    const Line L = make_line(r0, delta, N, tid);
+    double uc[NC], uh[NC], ec, eh = 0.0;
+    vec2<double> abc, abh = {0.0, 0.0};
 #pragma unroll
-  for (int ch = 0; ch < C::NCH; ++ch) {
-    jv.fence();
-    double c[C::CH][DIM], vj[C::CH][DIM], pj[C::CH], aj[C::CH], bj[C::CH];
-    double uj[C::CH][IND == 0 ? NC : 1], etaj[C::CH];
-    int32_t jc[C::CH];
+    for (int q = 0; q < NC; ++q) uh[q] = 0.0;
+    if (self) {
 #pragma unroll
-    for (int kk = 0; kk < C::CH; ++kk) {
-      const int k = ch * C::CH + kk;
-      jc[kk] = jv[k];
-      const int64_t js = jc[kk] >= 0 ? jc[kk] : i;
-      jv.grad(k, c[kk]);
-      aj[kk] = aux[X::A * N + js];
-      bj[kk] = aux[X::B * N + js];
-      if constexpr (IND == 0) {
-        // the indicator needs the whole state; v and p follow from it
-        load_state<NC>(U, N, js, uj[kk]);
-        etaj[kk] = aux[X::ETA * N + js];
+      for (int q = 0; q < NC; ++q) uc[q] = ui[q];
+      abc = abi;
+      ec = etai;
+    } else {
+      line_state<NC>(U, N, L.b, L.c, uc);
+      abc = line_ld(reinterpret_cast<const vec2<double> *>(aux), L.b, L.c);
+      ec = IND == 0 ? line_ld(aux + X::ETA * N, L.b, L.c) : 0.0;
+    }
+    if (edge) {
+      line_state<NC>(U, N, L.b, L.h, uh);
+      abh = line_ld(reinterpret_cast<const vec2<double> *>(aux), L.b, L.h);
+      if (IND == 0) eh = line_ld(aux + X::ETA * N, L.b, L.h);
+    }
+    static_for<0, 3>([&](auto along) __attribute__((always_inline)) {
+      constexpr int dx = decltype(along)::value - 1;
+      if constexpr (self && (dx == 0 || (IND != 0 && dx < 0))) return;  // c_ii = 0
+      constexpr int k = 3 * ln + dx + 1, cls = slot_class<DIM>(k);
+      constexpr int o[3] = {dx, dy, dz};
+      double uj[NC], aj, bj, ej;
+      if (dx == 0) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) uj[q] = uc[q];
+        aj = abc.x; bj = abc.y; ej = ec;
       } else {
 #pragma unroll
-        for (int q = 0; q < DIM; ++q) vj[kk][q] = aux[q * N + js];
-        pj[kk] = aux[X::P * N + js];
+        for (int q = 0; q < NC; ++q) uj[q] = side(dx, uh[q], uc[q]);
+        aj = side(dx, abh.x, abc.x);
+        bj = side(dx, abh.y, abc.y);
+        ej = side(dx, eh, ec);
       }
-    }
+      double vj[DIM], pj, c[DIM], n[DIM];
+      vel_pres<DIM>(g, uj, vj, pj);
 #pragma unroll
-    for (int kk = 0; kk < C::CH; ++kk) {
-      const int k = ch * C::CH + kk;
-      const int32_t j = jc[kk];
-      if (j < 0) continue;
-      if constexpr (IND == 0) vel_pres<DIM>(g, uj[kk], vj[kk], pj[kk]);
-      double c2 = 0.0;
-#pragma unroll
-      for (int q = 0; q < DIM; ++q) c2 += c[kk][q] * c[kk][q];
-      const double cn = fast_sqrt(c2);
-      if constexpr (IND == 0) {
-        double fc[NC], vc = 0.0;
-#pragma unroll
-        for (int q = 0; q < DIM; ++q) vc += vj[kk][q] * c[kk][q];
-        flux_dot<DIM>(uj[kk], vj[kk], pj[kk], c[kk], fc);
-        double t = etaj[kk] * vc;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) t -= etap[q] * fc[q];
-        num += t;
-        den += fabs(t);
-        scl += cn * aj[kk] * (uj[kk][0] + fabs(etaj[kk]));
+      for (int q = 0; q < DIM; ++q) {
+        c[q] = o[q] < 0 ? -geo_ld(&geo->ic[cls][q]) : geo_ld(&geo->ic[cls][q]);
+        n[q] = o[q] < 0 ? -geo_ld(&geo->inrm[cls][q]) : geo_ld(&geo->inrm[cls][q]);
       }
-      if (j > i) {
-        const int64_t e = eidx<DIM>(k, i);
-        const double icn = fast_rcp(cn);
-        double uL = 0.0, uR = 0.0;
-#pragma unroll
-        for (int q = 0; q < DIM; ++q) {
-          uL += vi[q] * c[kk][q] * icn;
-          uR += vj[kk][q] * c[kk][q] * icn;
+      const double cn = geo_ld(&geo->icn[cls]);
+      if constexpr (IND == 0)
+        indicator_term<DIM, cls>(etap, uj, vj, pj, aj, ej, c, cn, num, den, scl);
+      if constexpr (k > W / 2) {
+        const double uL = dot_c<DIM, cls>(vi, n), uR = dot_c<DIM, cls>(vj, n);
+        const LT dst =
+            to_lt_up<LT>(lambda_max<SEV>(g, uL, pi, abi.x, abi.y, uR, pj, aj, bj) * cn);
+        if (act) {
+          st_once<LT>(edge_at<DIM>(d, r0, k, e0), dst);
+          st_once<LT>(edge_t<DIM>(d, r0 + delta + dx, tslot<DIM>(k), tid), dst);
         }
-        double dij = lambda_max<SEV>(g, uL, pi, ai, bi, uR, pj[kk], aj[kk], bj[kk]) * cn;
-        const int kt = tslot<DIM>(k);
-        const int64_t et = eidx<DIM>(kt, j);
-        if (wall_i) {
-          // both ends may be on the wall: c_ji != -c_ij, take both directions
-          double ct[DIM];
-          grad_transposed<DIM>(k, c[kk], ct);
-          double ct2 = 0.0;
-#pragma unroll
-          for (int q = 0; q < DIM; ++q) ct2 += ct[q] * ct[q];
-          const double ctn = fast_sqrt(ct2);
-          const double ictn = fast_rcp(ctn);
-          double uLt = 0.0, uRt = 0.0;
-#pragma unroll
-          for (int q = 0; q < DIM; ++q) {
-            uLt += vj[kk][q] * ct[q] * ictn;
-            uRt += vi[q] * ct[q] * ictn;
-          }
-          dij = fmax(dij, lambda_max<SEV>(g, uLt, pj[kk], aj[kk], bj[kk], uRt, pi, ai, bi) * ctn);
-        }
-        const LT dst = to_lt_up<LT>(dij);
-        st_once(&d[e], dst);
-        st_once(&d[et], dst);
       }
-    }
-  }
-  // (an isolated node -- a padding row of a pack -- has den = scl = 0)
-  if constexpr (IND == 0)
-    alpha[i] = to_lt<LT>(den + scl > 0.0 ? fabs(num) / (den + 1e-2 * scl) : 0.0);
-  else if constexpr (IND == 1) alpha[i] = LT(1);
-  else alpha[i] = LT(0);
+    });
+    line_keep(num, den, scl);
+  });
+  if (act) alpha[r0 + tid] = alpha_of<IND, LT>(num, den, scl);
 }
 
 // FP32 evaluation (mixed-precision mode with FP32 arithmetic, entropy
@@ -397,7 +656,8 @@ __device__ __forceinline__ void visc_row_f32(const DevGraphT<LT> &G,
   double ui[NC], vi[DIM], pi;
   load_state<NC>(U, N, i, ui);
   const double eps_i = vel_pres<DIM>(g, ui, vi, pi);  // FP64 (the fallback needs it)
-  const double ai = aux[X::A * N + i], bi = aux[X::B * N + i];
+  const double2 abi = aux_ab(aux, i);
+  const double ai = abi.x, bi = abi.y;
   const bool wall_i = G.wall[i] != 0;
   // entropy variables of row i, formed in FP64 once per row
   float etap[NC], vif[DIM];
@@ -428,8 +688,9 @@ __device__ __forceinline__ void visc_row_f32(const DevGraphT<LT> &G,
       jc[kk] = jv[k];
       const int64_t js = jc[kk] >= 0 ? jc[kk] : i;
       jv.grad(k, c[kk]);
-      aj[kk] = aux[X::A * N + js];
-      bj[kk] = aux[X::B * N + js];
+      const double2 abj = aux_ab(aux, js);
+      aj[kk] = abj.x;
+      bj[kk] = abj.y;
       load_state<NC>(U, N, js, uj[kk]);
       etaj[kk] = aux[X::ETA * N + js];
     }
@@ -536,7 +797,12 @@ __global__ __launch_bounds__(kBlock) void k_visc(DevGraphT<LT> G,
                                                  LT *__restrict__ d,
                                                  LT *__restrict__ alpha,
                                                  Gas g) {
-  visc_row<DIM, IND, SEV, LT>(G, U, aux, d, alpha, g, blockIdx.x, row_id());
+  const uint32_t ns = spec_blocks<DIM>(G);
+  if (blockIdx.x < ns) {
+    visc_spec<DIM, IND, SEV, LT>(G, U, aux, d, alpha, g);
+  } else {
+    visc_lines<DIM, IND, SEV, LT>(G, U, aux, d, alpha, g, blockIdx.x - ns);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -612,109 +878,59 @@ __global__ __launch_bounds__(1024) void k_dt_final(const double *__restrict__ pa
 
 // ---------------------------------------------------------------------------
 // Low-order update, bounds and high-order flux (stored divided by m_i).
-// first: the lane that empties the limiter work lists of this stage
+//
+// Sums of a row.  sum_j (f(U_j) - f(U_i)) c_ij: the row's own flux enters
+// once, against the sum of c_ij over the off-diagonal entries (0 on interior
+// rows); only its density component is needed entry by entry, for the bar
+// states.
+template <int DIM>
+struct LoSums {
+  static constexpr int NC = DIM + 2;
+  double acc[NC], fh[NC], rmin, rmax, phimin, dsum;
+};
+
+// Adds entry (i,j): U_j with velocity and pressure, c_ij, d_ij, Phi_j and
+// dH_ij.  The arithmetic of interior and other rows, spelled out once.
+template <int DIM, int MASK, bool PRED = false>
+__device__ __forceinline__ void lo_term(const double *ui, const double *vi, const double *uj,
+                                        const double *vj, double pj, const double *c,
+                                        double dk, double dH, double phij, LoSums<DIM> &S,
+                                        bool there = true) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  double fc[DIM + 2];
+  flux_c<DIM, MASK>(uj, dot_c<DIM, MASK>(vj, c), pj, c, fc);
+  const double vci = dot_c<DIM, MASK>(vi, c);
+  // density of the bar state (eq. bar_state) for the local bounds
+  double rbar = fma(-fma(-ui[0], vci, fc[0]), fast_rcp(2.0 * dk), 0.5 * (ui[0] + uj[0]));
+  if (PRED) rbar = there ? rbar : ui[0];
+  S.rmin = fmin(S.rmin, rbar);
+  S.rmax = fmax(S.rmax, rbar);
+  S.phimin = fmin(S.phimin, phij);
+#pragma unroll
+  for (int q = 0; q < DIM + 2; ++q) {
+    const double du = uj[q] - ui[q];
+    S.acc[q] += fma(dk, du, -fc[q]);
+    S.fh[q] += fma(dH, du, -fc[q]);
+  }
+  S.dsum += dk;
+}
+
+// U^L, F^H/m_i, bounds and flags of row i from its sums.
 template <int DIM, typename LT>
-__device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
-                                       const Gas &g, uint32_t blk, int64_t i, bool first) {
-  using X = Aux<DIM>;
-  using C = Cfg<DIM, NS_CH_LO>;
-  constexpr int NC = C::NC;
+__device__ __forceinline__ void lo_store(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                         int64_t i, int mem, double tau, const double *ui,
+                                         LT ali, const LoSums<DIM> &S) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  constexpr int NC = DIM + 2;
   const int64_t N = G.N;
-  if (first) {
-    A.qcnt[0] = 0;
-    A.qcnt[1] = 0;
-    if (A.drow) A.qcnt[2] = 0;
-  }
-  if (i >= N) return;
-  const double *__restrict__ U = A.U;
-  const double *__restrict__ aux = A.aux;
-  const LT *__restrict__ alpha = A.alpha;
-  const LT *__restrict__ dd = A.d;
-  BoxNbr<DIM> jv = block_nbr<DIM>(G, blk, i);
-  double ui[NC], vi[DIM], pi;
-  load_state<NC>(U, N, i, ui);
-  vel_pres<DIM>(g, ui, vi, pi);
-  const double ali = alpha[i];
-  const int mem = member(A, i);
-  const double tau = A.tau[mem];
-  double acc[NC], fh[NC];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) { acc[q] = 0.0; fh[q] = 0.0; }
-  double rmin = ui[0], rmax = ui[0], phimin = aux[X::PHI * N + i], dsum = 0.0;
-  // sum_j (f(U_j) - f(U_i)) c_ij: the row's own flux enters once, against
-  // the sum of c_ij over the off-diagonal entries (only its density
-  // component is needed entry by entry, for the bar states)
-  double csum[DIM];
-#pragma unroll
-  for (int k = 0; k < DIM; ++k) csum[k] = 0.0;
-  double vci = 0.0;  // v_i . c_ij of the current entry
-#pragma unroll
-  for (int ch = 0; ch < C::NCH; ++ch) {
-    jv.fence();
-    double c[C::CH][DIM], uj[C::CH][NC], phij[C::CH], alj[C::CH], dij[C::CH];
-    int32_t jc[C::CH];
-#pragma unroll
-    for (int kk = 0; kk < C::CH; ++kk) {
-      const int k = ch * C::CH + kk;
-      const int64_t e = eidx<DIM>(k, i);
-      jc[kk] = jv[k];
-      const int64_t js = jc[kk] >= 0 ? jc[kk] : i;
-      jv.grad(k, c[kk]);
-      load_state<NC>(U, N, js, uj[kk]);  // v and p follow from it
-      phij[kk] = aux[X::PHI * N + js];
-      alj[kk] = alpha[js];
-      dij[kk] = ld_once(&dd[e]);
-    }
-#pragma unroll
-    for (int kk = 0; kk < C::CH; ++kk) {
-      const int32_t j = jc[kk];
-      if (j < 0) continue;
-      if (j == i) {
-        double fci[NC];
-        flux_dot<DIM>(ui, vi, pi, c[kk], fci);
-#pragma unroll
-        for (int q = 0; q < NC; ++q) fh[q] -= fci[q];
-        continue;
-      }
-      vci = 0.0;
-#pragma unroll
-      for (int k = 0; k < DIM; ++k) {
-        vci += vi[k] * c[kk][k];
-        csum[k] += c[kk][k];
-      }
-      double fcj[NC], vj[DIM], pj;
-      vel_pres<DIM>(g, uj[kk], vj, pj);
-      flux_dot<DIM>(uj[kk], vj, pj, c[kk], fcj);
-      const double dk = dij[kk];
-      // density of the bar state (eq. bar_state) for the local bounds
-      const double rbar = 0.5 * (ui[0] + uj[kk][0]) - (fcj[0] - ui[0] * vci) * fast_rcp(2.0 * dk);
-      rmin = fmin(rmin, rbar);
-      rmax = fmax(rmax, rbar);
-      phimin = fmin(phimin, phij[kk]);
-      const double dH = 0.5 * (ali + alj[kk]) * dk;
-#pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        const double du = uj[kk][q] - ui[q];
-        acc[q] += dk * du - fcj[q];
-        fh[q] += -fcj[q] + dH * du;
-      }
-      dsum += dk;
-    }
-  }
-  {
-    double fcs[NC];
-    flux_dot<DIM>(ui, vi, pi, csum, fcs);
-#pragma unroll
-    for (int q = 0; q < NC; ++q) acc[q] += fcs[q];
-  }
   const double rmi = G.rmi[i];
   const double tm = tau * rmi;
   double ul[NC];
   LT fs[NC];
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    ul[q] = ui[q] + tm * acc[q];
-    fs[q] = to_lt<LT>(fh[q] * rmi);
+    ul[q] = fma(tm, S.acc[q], ui[q]);
+    fs[q] = to_lt<LT>(S.fh[q] * rmi);
   }
   store_state<NC>(A.UL, N, i, ul);
   if constexpr (DIM == 3) {
@@ -723,12 +939,12 @@ __device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<
     LT f6[NC + 1];
 #pragma unroll
     for (int q = 0; q < NC; ++q) f6[q] = fs[q];
-    f6[NC] = alpha[i];
+    f6[NC] = ali;
     store_state<NC + 1>(A.FH, N, i, f6);
   } else {
     store_state<NC>(A.FH, N, i, fs);
   }
-  if (A.check_cfl && tau > G.mi[i] / (2.0 * dsum)) A.flags[4 * mem] = 1;
+  if (A.check_cfl && tau > G.mi[i] / (2.0 * S.dsum)) A.flags[4 * mem] = 1;
   if (A.check_low) {
     double m2 = 0.0;
 #pragma unroll
@@ -736,14 +952,268 @@ __device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<
     if (!(ul[0] > 0.0) || !(ul[NC - 1] - 0.5 * m2 / ul[0] > 0.0)) A.flags[4 * mem + 3] = 1;
   }
   const double r = G.rrel[i];
-  const double bv[3] = {(1.0 - r) * rmin, (1.0 + r) * rmax, (1.0 - r) * phimin};
+  const double bv[3] = {(1.0 - r) * S.rmin, (1.0 + r) * S.rmax, (1.0 - r) * S.phimin};
   store_state<3>(A.bnds, N, i, bv);
+}
+
+// first: the lane that empties the limiter work lists of this stage
+template <typename LT>
+__device__ __forceinline__ void clear_lists(const StageArgsT<LT> &A, bool first) {
+  if (first) {
+    A.qcnt[0] = 0;
+    A.qcnt[1] = 0;
+    if (A.drow) A.qcnt[2] = 0;
+  }
+}
+
+// The general path (see visc_line): adds the entries of line l of row i;
+// csum is the sum of c_ij, the diagonal entry's flux goes to F^H directly.
+template <int DIM, bool ANY, typename LT>
+__device__ __forceinline__ void lo_line(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                        const Gas &g, const BoxNbr<DIM> &jv, int64_t i,
+                                        const double *ui, const double *vi, double pi,
+                                        double ali, int l, LoSums<DIM> &S, double *csum) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  constexpr int NC = DIM + 2, ALL = (1 << DIM) - 1, C = Cfg<DIM>::W / 2;
+  const int64_t N = G.N;
+  double uj[3][NC], phij[3], alj[3], dl[3];
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    const int32_t j = jv[3 * l + t];
+    const int64_t js = j >= 0 ? j : i;
+    load_state<NC>(A.U, N, js, uj[t]);
+    phij[t] = A.aux[Aux<DIM>::PHI * N + js];
+    alj[t] = A.alpha[js];
+    dl[t] = ld_once(&A.d[eidx<DIM>(3 * l + t, i)]);
+  }
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int k = 3 * l + t;
+    const bool there = jv[k] >= 0;
+    double c[DIM];
+    jv.grad(k, c);
+    if (k == C) {
+      if (!(ANY && jv.interior())) {  // c_ii = 0 there
+        double fci[NC];
+        flux_c<DIM, ALL>(ui, dot_c<DIM, ALL>(vi, c), pi, c, fci);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) S.fh[q] -= fci[q];
+      }
+      continue;
+    }
+    const double dk = there ? dl[t] : 0.0;
+#pragma unroll
+    for (int q = 0; q < DIM; ++q) {
+      c[q] = there ? c[q] : 0.0;
+      csum[q] += c[q];
+    }
+    double vj[DIM], pj;
+    vel_pres<DIM>(g, uj[t], vj, pj);
+    lo_term<DIM, ALL, true>(ui, vi, uj[t], vj, pj, c, dk, 0.5 * (ali + alj[t]) * dk, phij[t],
+                            S, there);
+  }
+}
+
+template <int DIM>
+__device__ __forceinline__ void lo_clear(LoSums<DIM> &S, double rho, double phi) {
+#pragma unroll
+  for (int q = 0; q < DIM + 2; ++q) { S.acc[q] = 0.0; S.fh[q] = 0.0; }
+  S.rmin = S.rmax = rho;
+  S.phimin = phi;
+  S.dsum = 0.0;
+}
+
+// Adds the row's own flux against the sum of c_ij.
+template <int DIM>
+__device__ __forceinline__ void lo_own_flux(const double *ui, const double *vi, double pi,
+                                            const double *csum, LoSums<DIM> &S) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  constexpr int NC = DIM + 2, ALL = (1 << DIM) - 1;
+  double fcs[NC];
+  flux_c<DIM, ALL>(ui, dot_c<DIM, ALL>(vi, csum), pi, csum, fcs);
+#pragma unroll
+  for (int q = 0; q < NC; ++q) S.acc[q] += fcs[q];
+}
+
+// A listed row, shared by the lanes of its lines.
+template <int DIM, typename LT>
+__device__ __forceinline__ void lo_spec(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                        const Gas &g) {
+  constexpr int NC = DIM + 2;
+  const SpecLane<DIM> L(G);
+  const int64_t i = L.i;
+  double ui[NC], vi[DIM], pi, csum[DIM];
+  load_state<NC>(A.U, G.N, i, ui);
+  vel_pres<DIM>(g, ui, vi, pi);
+  const LT al = A.alpha[i];
+  LoSums<DIM> S;
+  lo_clear(S, ui[0], A.aux[Aux<DIM>::PHI * G.N + i]);
+#pragma unroll
+  for (int q = 0; q < DIM; ++q) csum[q] = 0.0;
+  lo_line<DIM, false>(G, A, g, row_nbr<DIM>(G, i), i, ui, vi, pi, (double)al, L.line, S, csum);
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    S.acc[q] = L.sum(S.acc[q]);
+    S.fh[q] = L.sum(S.fh[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < DIM; ++q) csum[q] = L.sum(csum[q]);
+  S.rmin = L.least(S.rmin);
+  S.rmax = -L.least(-S.rmax);
+  S.phimin = L.least(S.phimin);
+  S.dsum = L.sum(S.dsum);
+  lo_own_flux<DIM>(ui, vi, pi, csum, S);
+  if (L.ok && L.line == 0) {
+    const int mem = member(A, i);
+    lo_store<DIM>(G, A, i, mem, A.tau[mem], ui, al, S);
+  }
+}
+
+// Any row by one lane (see visc_row).
+template <int DIM, typename LT>
+__device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                       const Gas &g, BoxNbr<DIM> jv, int64_t i) {
+  constexpr int NC = DIM + 2;
+  double ui[NC], vi[DIM], pi, csum[DIM], tc[DIM];
+  load_state<NC>(A.U, G.N, i, ui);
+  vel_pres<DIM>(g, ui, vi, pi);
+  const LT al = A.alpha[i];
+  const int mem = member(A, i);
+  const bool in = jv.interior();
+  LoSums<DIM> S, T;
+  lo_clear(S, ui[0], A.aux[Aux<DIM>::PHI * G.N + i]);
+  T = S;
+#pragma unroll
+  for (int q = 0; q < DIM; ++q) csum[q] = tc[q] = 0.0;
+#pragma unroll 1
+  for (int l = 0; l < Cfg<DIM>::W / 3; ++l) {
+    lo_line<DIM, true>(G, A, g, jv, i, ui, vi, pi, (double)al, l, S, csum);
+    if (!in) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        T.acc[q] += S.acc[q];
+        T.fh[q] += S.fh[q];
+        S.acc[q] = S.fh[q] = 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < DIM; ++q) {
+        tc[q] += csum[q];
+        csum[q] = 0.0;
+      }
+      T.dsum += S.dsum;
+      S.dsum = 0.0;
+    }
+  }
+  if (!in) {
+    T.rmin = S.rmin;
+    T.rmax = S.rmax;
+    T.phimin = S.phimin;
+    lo_own_flux<DIM>(ui, vi, pi, tc, T);
+    S = T;
+  }
+  lo_store<DIM>(G, A, i, mem, A.tau[mem], ui, al, S);
+}
+
+// The interior rows of row block blk, line by line (line_sweep.hpp).
+template <int DIM, typename LT>
+__device__ __forceinline__ void lo_lines(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                         const Gas &g, uint32_t blk) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  using X = Aux<DIM>;
+  constexpr int NC = DIM + 2, W = Cfg<DIM>::W;
+  const int64_t N = G.N, r0 = (int64_t)blk * kBlock;
+  uint32_t tid = threadIdx.x;
+  const uint32_t lane = tid & 63;
+  const BoxGeom *geo = block_geo(G, blk);
+  const int64_t n0 = geo_ld(&geo->n[0]), n01 = n0 * geo_ld(&geo->n[1]);
+  const bool act = line_row(G, r0 + tid);
+  const bool edge = ((lane + 1) & 63) < 2;  // lanes 63 and 0
+  const double *__restrict__ U = A.U;
+  const double *__restrict__ phi = A.aux + X::PHI * N;
+  const LT *__restrict__ alpha = A.alpha;
+  const LT *__restrict__ dd = A.d;
+  const Line own = make_line(r0, 0, N, tid);
+  double ui[NC], vi[DIM], pi;
+  line_state<NC>(U, N, own.b, own.c, ui);
+  vel_pres<DIM>(g, ui, vi, pi);
+  const LT al = line_ld(alpha, own.b, own.c);
+  const double ali = al;
+  LoSums<DIM> S;
+  lo_clear(S, ui[0], line_ld(phi, own.b, own.c));
+  const uint32_t e0 = min((tid >> 6), (uint32_t)((N - 1 - r0) >> 6)) * (W * 64) + lane;
+  static_for<0, W / 3>([&](auto line) __attribute__((always_inline)) {
+    constexpr int ln = decltype(line)::value;
+    constexpr int dy = ln % 3 - 1, dz = DIM == 3 ? ln / 3 - 1 : 0;
+    constexpr bool self = dy == 0 && dz == 0;
+    line_fence(tid);
+    const Line L = make_line(r0, dy * n0 + dz * n01, N, tid);
+    double uc[NC], uh[NC], ac, ah = 0.0, pc, ph = 0.0, dk[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (3 * ln + t != W / 2) dk[t] = ld_once<LT>(edge_at<DIM>(dd, r0, 3 * ln + t, e0));
+#pragma unroll
+    for (int q = 0; q < NC; ++q) uh[q] = 0.0;
+    if (self) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) uc[q] = ui[q];
+      ac = ali;
+      pc = line_ld(phi, own.b, own.c);
+    } else {
+      line_state<NC>(U, N, L.b, L.c, uc);
+      ac = line_ld(alpha, L.b, L.c);
+      pc = line_ld(phi, L.b, L.c);
+    }
+    if (edge) {
+      line_state<NC>(U, N, L.b, L.h, uh);
+      ah = line_ld(alpha, L.b, L.h);
+      ph = line_ld(phi, L.b, L.h);
+    }
+    static_for<0, 3>([&](auto along) __attribute__((always_inline)) {
+      constexpr int dx = decltype(along)::value - 1;
+      if constexpr (self && dx == 0) return;  // c_ii = 0
+      constexpr int k = 3 * ln + dx + 1, cls = slot_class<DIM>(k);
+      constexpr int o[3] = {dx, dy, dz};
+      double uj[NC], alj, phij;
+      if (dx == 0) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) uj[q] = uc[q];
+        alj = ac; phij = pc;
+      } else {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) uj[q] = side(dx, uh[q], uc[q]);
+        alj = side(dx, ah, ac);
+        phij = side(dx, ph, pc);
+      }
+      double vj[DIM], pj, c[DIM];
+      vel_pres<DIM>(g, uj, vj, pj);
+#pragma unroll
+      for (int q = 0; q < DIM; ++q)
+        c[q] = o[q] < 0 ? -geo_ld(&geo->ic[cls][q]) : geo_ld(&geo->ic[cls][q]);
+      lo_term<DIM, cls>(ui, vi, uj, vj, pj, c, dk[dx + 1], 0.5 * (ali + alj) * dk[dx + 1],
+                        phij, S);
+      // (one slot at a time: three at once cost a wave per SIMD in 3D)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) line_keep(S.acc[q], S.fh[q]);
+      line_keep(S.rmin, S.rmax, S.phimin, S.dsum);
+      if constexpr (DIM == 3) __builtin_amdgcn_sched_barrier(0);
+    });
+  });
+  if (act) {
+    const int mem = A.seg ? geo_ld(&A.seg[blk]) : 0;
+    lo_store<DIM>(G, A, r0 + tid, mem, A.tau[mem], ui, al, S);
+  }
 }
 
 template <int DIM, typename LT>
 __global__ __launch_bounds__(kBlock) void k_lo(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
-  const int64_t i = row_id();
-  lo_row<DIM, LT>(G, A, g, blockIdx.x, i, i == 0);
+  clear_lists(A, row_id() == 0);
+  const uint32_t ns = spec_blocks<DIM>(G);
+  if (blockIdx.x < ns) {
+    lo_spec<DIM>(G, A, g);
+  } else {
+    lo_lines<DIM>(G, A, g, blockIdx.x - ns);
+  }
 }
 
 // P_ij = tau/(m_i lambda_i) (b_ij F_j - b_ji F_i + (dH - d)(U_j - U_i)) with
@@ -833,7 +1303,7 @@ __device__ __forceinline__ void finish(const DevGraphT<LT> &G, const StageArgsT<
     double un[NC];
     load_state<NC>(A.Un, N, i, un);
 #pragma unroll
-    for (int q = 0; q < NC; ++q) w[q] = A.sa * un[q] + A.sb * u[q];
+    for (int q = 0; q < NC; ++q) w[q] = fma(A.sa, un[q], A.sb * u[q]);
   } else {
 #pragma unroll
     for (int q = 0; q < NC; ++q) w[q] = A.sb * u[q];
@@ -1424,7 +1894,7 @@ __device__ __forceinline__ void slip_one(int t, int end, const int32_t *__restri
 #pragma unroll
   for (int k = 0; k < DIM; ++k) {
     n[k] = nrm[(int64_t)k * stride + t];
-    mn += U[node_at(DIM + 2, 1 + k, i, N)] * n[k];
+    mn = fma(U[node_at(DIM + 2, 1 + k, i, N)], n[k], mn);
   }
 #pragma unroll
   for (int k = 0; k < DIM; ++k) U[node_at(DIM + 2, 1 + k, i, N)] -= mn * n[k];
@@ -1840,13 +2310,19 @@ __global__ __launch_bounds__(kBlock) void k_persist(DevGraphT<LT> G, PersistArgs
     const uint32_t blk = kind == PK_ROW ? (uint32_t)mb0 + r : 0u;
     const int64_t i = (int64_t)blk * kBlock + tid;
     switch (ph) {
-      case PP_PRIM: prim_row<DIM, false>(G.N, A.U, A.aux, g, i); break;
-      case PP_VISC: visc_row<DIM, 0, SEV, LT>(G, A.U, A.aux, A.d, A.alpha, g, blk, i); break;
+      case PP_PRIM: prim_row<DIM>(G.N, A.U, A.aux, g, i); break;
+      case PP_VISC:
+        if (i < G.N)
+          visc_row<DIM, SEV, LT>(G, A.U, A.aux, A.d, A.alpha, g, block_nbr<DIM>(G, blk, i), i);
+        break;
       case PP_DTP: dt_partial_blk<DIM, LT>(G, A.d, A.partial, blk, i); break;
       case PP_DTF:
         dt_final_member(A.partial, mb0, mb1, P.cfl, A.tau + m, P.tacc + m);
         break;
-      case PP_LO: lo_row<DIM, LT>(G, A, g, blk, i, r == 0 && tid == 0); break;
+      case PP_LO:
+        clear_lists(A, r == 0 && tid == 0);
+        if (i < G.N) lo_row<DIM>(G, A, g, block_nbr<DIM>(G, blk, i), i);
+        break;
       case PP_LIM1: lim1_row<DIM, SEV, LT>(G, A, g, blk, i); break;
       case PP_ROOT1: root_range<DIM, 1, SEV, LT>(G, A, g, r * kBlock + tid, nr * kBlock); break;
       case PP_LIM2: lim2_row<DIM, DIM == 2 ? 0 : 3, SEV, LT>(G, A, g, blk, i); break;
@@ -1887,18 +2363,15 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                 double cfl, hipStream_t s, void (*before)(void *, const char *),
                 void (*after)(void *), void *prof) {
   const dim3 grid = grid_for(G.N), block(kBlock);
+  // sweeps along stencil lines: the listed rows' blocks in front
+  const dim3 lgrid(grid.x + spec_blocks<DIM>(G));
 #define NS_LAUNCH(name, ...)                                  \
   do {                                                        \
     before(prof, name);                                       \
     __VA_ARGS__;                                              \
     after(prof);                                              \
   } while (0)
-  if (indicator == 0)
-    NS_LAUNCH("prim", hipLaunchKernelGGL((k_prim<DIM, false>), grid, block, 0, s, G.N, A.U,
-                                         A.aux, gas));
-  else
-    NS_LAUNCH("prim", hipLaunchKernelGGL((k_prim<DIM, true>), grid, block, 0, s, G.N, A.U,
-                                         A.aux, gas));
+  NS_LAUNCH("prim", hipLaunchKernelGGL(k_prim<DIM>, grid, block, 0, s, G.N, A.U, A.aux, gas));
   bool f32 = false;
   if constexpr (SEV == 1 && sizeof(LT) == 4) {
     if (indicator == 0 && A.fp32_eval) {
@@ -1909,13 +2382,13 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
   }
   if (f32) {
   } else if (indicator == 0)
-    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 0, SEV, LT>), grid, block, 0, s, G,
+    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 0, SEV, LT>), lgrid, block, 0, s, G,
                                          A.U, A.aux, A.d, A.alpha, gas));
   else if (indicator == 1)
-    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 1, SEV, LT>), grid, block, 0, s, G,
+    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 1, SEV, LT>), lgrid, block, 0, s, G,
                                          A.U, A.aux, A.d, A.alpha, gas));
   else
-    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), grid, block, 0, s, G,
+    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), lgrid, block, 0, s, G,
                                          A.U, A.aux, A.d, A.alpha, gas));
   if (auto_dt) {
     NS_LAUNCH("dt_partial", hipLaunchKernelGGL((k_dt_partial<DIM, LT>), grid, block, 0, s,
@@ -1928,7 +2401,7 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
       NS_LAUNCH("dt_final", hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(1024), 0, s,
                                                A.partial, (int64_t)grid.x, cfl, A.tau));
   }
-  NS_LAUNCH("lo", hipLaunchKernelGGL((k_lo<DIM, LT>), grid, block, 0, s, G, A, gas));
+  NS_LAUNCH("lo", hipLaunchKernelGGL((k_lo<DIM, LT>), lgrid, block, 0, s, G, A, gas));
   if (limiter == 1) {
     NS_LAUNCH("combine", hipLaunchKernelGGL((k_combine_low<DIM, LT>), grid, block, 0, s,
                                             G, A));
@@ -1988,11 +2461,12 @@ void dt_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A, do
              hipStream_t s, void (*before)(void *, const char *),
              void (*after)(void *), void *prof) {
   const dim3 grid = grid_for(G.N), block(kBlock);
+  const dim3 lgrid(grid.x + spec_blocks<DIM>(G));
   before(prof, "prim");
-  hipLaunchKernelGGL((k_prim<DIM, true>), grid, block, 0, s, G.N, A.U, A.aux, gas);
+  hipLaunchKernelGGL(k_prim<DIM>, grid, block, 0, s, G.N, A.U, A.aux, gas);
   after(prof);
   before(prof, "visc_dt");
-  hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), grid, block, 0, s, G, A.U, A.aux, A.d,
+  hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), lgrid, block, 0, s, G, A.U, A.aux, A.d,
                      A.alpha, gas);
   after(prof);
   before(prof, "dt_partial");

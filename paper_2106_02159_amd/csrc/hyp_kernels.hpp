@@ -6,9 +6,11 @@
 // node i at c*N + i); edge arrays are sliced ELL (rows in slices of 64, slot-major
 // within a slice: slot k of row i at ((i/64) W + k) 64 + i%64), so lane i of
 // a wavefront reading slot k of its row produces one coalesced access.  One
-// lane owns one row; neighbour data are gathered through the L1/L2 caches.  Sweeps, in dependency order (each needs the
+// lane owns one row; the viscosity and low-order sweeps read the neighbours
+// along stencil lines (line_sweep.hpp), the limiter sweeps gather them through
+// the L1/L2 caches.  Sweeps, in dependency order (each needs the
 // previous one complete over the whole mesh):
-//   k_prim   per node: v, p, sound speed a, a p^(-(g-1)/(2g)), eta, Phi
+//   k_prim   per node: sound speed a, a p^(-(g-1)/(2g)), eta, Phi
 //   k_visc   d^L_ij for j > i (Sec. 3.1), written to (i,j) and (j,i);
 //            indicator alpha_i (Sec. 3.2)
 //   k_dt     (auto time step only) per-block min of m_i / (2 sum_j d_ij)
@@ -56,6 +58,11 @@ struct DevGraphT {
   const double *crm;    // N: (|I(i)| - 1) / m_i = 1 / (lambda_i m_i)
   const double *rrel;   // N: bound relaxation r_i
   const uint8_t *wall;  // N
+  // rows that the line path does not handle (line_sweep.hpp): the ends of
+  // the meshes and padding rows; flag per row, and their list
+  const uint8_t *spec;
+  const int32_t *srow;
+  int nsrow;
 };
 
 template <typename LT>
@@ -63,7 +70,7 @@ struct StageArgsT {
   const double *U;   // stage input, nc*N
   const double *Un;  // state at the start of the step (SSP combination)
   double *out;       // stage output, nc*N
-  double *aux;       // (dim+5)*N
+  double *aux;       // 4*N: (a, b) per node, eta, Phi
   LT *alpha;         // N
   LT *d;             // W*Np (FP32: rounded up, still an upper bound)
   double *UL;        // nc*N

@@ -141,6 +141,10 @@ struct ns_solver {
         *lt2f = nullptr;
   double *mi = nullptr, *rmi = nullptr, *lfac = nullptr, *crm = nullptr, *rrel = nullptr;
   uint8_t *wall = nullptr;
+  // rows off the line path (line_sweep.hpp): flag per row, list
+  uint8_t *spec = nullptr;
+  int32_t *srow = nullptr;
+  int nsrow = 0;
   int nslip = 0;
   int32_t *slip_idx = nullptr;
   double *slip_n = nullptr;
@@ -210,12 +214,14 @@ struct ns_solver {
     ns::DevGraph g;
     g.N = N; g.W = W; g.geo = geo; g.seg = seg;
     g.mi = mi; g.rmi = rmi; g.lfac = lfac; g.crm = crm; g.rrel = rrel; g.wall = wall;
+    g.spec = spec; g.srow = srow; g.nsrow = nsrow;
     return g;
   }
   ns::DevGraphT<float> devgraph32() const {
     ns::DevGraphT<float> g;
     g.N = N; g.W = W; g.geo = geo; g.seg = seg;
     g.mi = mi; g.rmi = rmi; g.lfac = lfac; g.crm = crm; g.rrel = rrel; g.wall = wall;
+    g.spec = spec; g.srow = srow; g.nsrow = nsrow;
     return g;
   }
   ns::StageArgsT<float> args32(int in, int out, double sa, double sb, int check) const {
@@ -705,6 +711,8 @@ ns::BoxGeom box_geom(const ns::MeshGraph &m, int64_t base) {
     b.m_inner[d] = b.m_end[d] = b.m_off[d] = 1.0;
     if (d < m.dim) m.m1_values(d, &b.m_inner[d], &b.m_end[d], &b.m_off[d]);
   }
+  if (m.dim == 2) ns::fill_interior<2>(&b);
+  else ns::fill_interior<3>(&b);
   return b;
 }
 
@@ -793,6 +801,13 @@ int64_t slip_count(const ns::MeshGraph &m) {
   return m.N - interior;
 }
 
+// Nodes that are not interior (an end of the mesh along some direction).
+int64_t end_count(const ns::MeshGraph &m) {
+  int64_t interior = 1;
+  for (int d = 0; d < m.dim; ++d) interior *= std::max<int64_t>(m.n[d] - 2, 0);
+  return m.N - interior;
+}
+
 int64_t footprint(const Layout &Lt, const ns_params *p) {
   const ns::MeshGraph &m = *Lt.mgs[0];
   const int64_t N = Lt.N, Np = Lt.Np, W = m.W, dim = m.dim, nc = dim + 2;
@@ -800,11 +815,17 @@ int64_t footprint(const Layout &Lt, const ns_params *p) {
   const int64_t nblocks = (N + ns::kBlock - 1) / ns::kBlock;
   const int64_t nm = (int64_t)Lt.mgs.size();
   int64_t nslip = 0;
-  for (const ns::MeshGraph *g : Lt.mgs) nslip += slip_count(*g);
+  int64_t nend = 0;
+  for (const ns::MeshGraph *g : Lt.mgs) {
+    nslip += slip_count(*g);
+    nend += end_count(*g) - g->N;
+  }
+  nend += N;  // padding rows too
   int64_t b = 0;
   b += nm * (int64_t)sizeof(ns::BoxGeom);             // box geometry
-  b += 5 * N * 8 + N;                                // m_i, 1/m_i, lfac, lfac/m_i, r_i, wall
-  b += 3 * nc * N * 8 + (dim + 5) * N * 8;           // states, aux
+  b += 5 * N * 8 + 2 * N;                            // m_i, 1/m_i, lfac, lfac/m_i, r_i, wall, spec
+  b += nend * 4;                                     // rows off the line path
+  b += 3 * nc * N * 8 + 4 * N * 8;                   // states, aux
   b += N * L + W * Np * L + nc * N * 8 + (nc + (dim == 3)) * N * L;  // alpha, d, U^L, F^H
   b += 3 * N * 8 + 2 * W * Np * L + nc * N * 8;      // bounds, l~ (2), U^(1)
   b += N * 4;                                        // pass-2 weight mask
@@ -926,8 +947,9 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
   NS_ALLOC(s->crm, N);
   NS_ALLOC(s->rrel, N);
   NS_ALLOC(s->wall, N);
+  NS_ALLOC(s->spec, N);
   for (int b = 0; b < 3; ++b) NS_ALLOC(s->S[b], nc * N);
-  NS_ALLOC(s->aux, (dim + 5) * N);
+  NS_ALLOC(s->aux, 4 * N);
   if (s->mixed) {
     NS_ALLOC(s->alphaf, N);
     NS_ALLOC(s->df, W * Np);
@@ -1029,6 +1051,24 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
       for (int q = 0; q < dim; ++q) snrm[(size_t)q * s->nslip + t] = nrm[(size_t)t * dim + q];
     NS_ALLOC(s->slip_idx, s->nslip);
     NS_ALLOC(s->slip_n, dim * s->nslip);
+    // rows off the line path: the ends of the meshes and padding rows
+    std::vector<uint8_t> spec(N, 1);
+    std::vector<int32_t> srow;
+    for (int r = 0; r < nm; ++r) {
+      const ns::MeshGraph &m = *Lt.mgs[r];
+      const int64_t b0 = Lt.base[r];
+      int64_t a[3] = {0, 0, 0};
+      for (int64_t i = 0; i < m.N; ++i) {
+        bool end = false;
+        for (int d = 0; d < (int)dim; ++d) end = end || a[d] == 0 || a[d] == m.n[d] - 1;
+        if (end) srow.push_back((int32_t)(b0 + i));
+        else spec[b0 + i] = 0;
+        for (int d = 0; d < (int)dim && ++a[d] == m.n[d]; ++d) a[d] = 0;
+      }
+      for (int64_t i = b0 + m.N; i < mend(r); ++i) srow.push_back((int32_t)i);
+    }
+    s->nsrow = (int)srow.size();
+    NS_ALLOC(s->srow, s->nsrow);
     // member of every workgroup, workgroup offsets of the members
     std::vector<int32_t> hseg, hmblk;
     if (s->pack) {
@@ -1067,6 +1107,8 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
         {s->crm, crm.data(), N * sizeof(double)},
         {s->rrel, rrel.data(), N * sizeof(double)},
         {s->wall, wall.data(), (size_t)N},
+        {s->spec, spec.data(), (size_t)N},
+        {s->srow, srow.data(), srow.size() * sizeof(int32_t)},
         {s->slip_idx, sidx.data(), sidx.size() * sizeof(int32_t)},
         {s->slip_n, snrm.data(), snrm.size() * sizeof(double)},
         {s->seg, hseg.data(), hseg.size() * sizeof(int32_t)},
