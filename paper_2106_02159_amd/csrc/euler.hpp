@@ -126,29 +126,47 @@ __device__ __forceinline__ float lambda_max_f32(const Gas &g, float uL, float pL
   return lam;
 }
 
+// x^(7/5) for x > 0: x z with z = x^(2/5) from two Newton steps for z^5 = x^2
+// on an FP32 start (relative error e -> 2 e^2: 1e-6, 2e-12, rounding), x
+// scaled by a power of 2^5 into the FP32 range first.  A quarter of pow's
+// instructions; within 3 ulp of it.
+__device__ __forceinline__ double pow_seven_fifths(double x) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  const int k = (__builtin_amdgcn_frexp_exp(x) * 205) >> 10;  // about e / 5
+  const double y = ldexp(x, -5 * k), y2 = y * y;
+  double z = (double)__builtin_amdgcn_exp2f(0.4f * __builtin_amdgcn_logf((float)y));
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const double z2 = z * z, z4 = z2 * z2;
+    z = fma(fma(-z4, z, y2), 0.2 * fast_rcp(z4), z);
+  }
+  return ldexp(y * z, 7 * k);
+}
+
 // psi(l) = eps(u + l P) - phi_min rho(u + l P)^gamma and its derivative.
-template <int DIM>
+template <int DIM, int SEV>
 __device__ __forceinline__ double psi_eval(const Gas &g, const double *u,
                                            const double *P, double l,
                                            double phi_min, double *dpsi) {
-  const double r = u[0] + l * P[0];
+#pragma clang fp contract(off)  // the same bits in every kernel
+  const double r = fma(l, P[0], u[0]);
   double m2 = 0.0, mp = 0.0;
 #pragma unroll
   for (int k = 0; k < DIM; ++k) {
-    const double mk = u[1 + k] + l * P[1 + k];
-    m2 += mk * mk;
-    mp += mk * P[1 + k];
+    const double mk = fma(l, P[1 + k], u[1 + k]);
+    m2 = fma(mk, mk, m2);
+    mp = fma(mk, P[1 + k], mp);
   }
-  const double E = u[DIM + 1] + l * P[DIM + 1];
+  const double E = fma(l, P[DIM + 1], u[DIM + 1]);
   const double ir = 1.0 / r;
-  const double eps = E - 0.5 * m2 * ir;
-  const double rg = pow(r, g.gamma);
+  const double eps = fma(-0.5 * m2, ir, E);
+  const double rg = SEV ? pow_seven_fifths(r) : pow(r, g.gamma);
   if (dpsi) {
     // d eps/dl = P_E - (m.P_m)/rho + |m|^2 P_rho / (2 rho^2)
-    const double deps = P[DIM + 1] - mp * ir + 0.5 * m2 * ir * ir * P[0];
-    *dpsi = deps - phi_min * g.gamma * rg * ir * P[0];
+    const double deps = fma(0.5 * m2 * ir * ir, P[0], fma(-mp, ir, P[DIM + 1]));
+    *dpsi = fma(-phi_min * g.gamma * rg * ir, P[0], deps);
   }
-  return eps - phi_min * rg;
+  return fma(-phi_min, rg, eps);
 }
 
 // Is u + l P inside the entropy bound Phi >= phi_min?  For gamma = 7/5 the
@@ -188,21 +206,22 @@ __device__ __forceinline__ bool entropy_ok(const Gas &g, const double *u,
 // the root at once.  Every candidate is checked by evaluating psi, so the
 // returned end is feasible even under round-off.  Stops when the bracket is
 // below 1e-14 (l is dimensionless, in [0,1]).
-template <int DIM>
+template <int DIM, int SEV>
 __device__ __forceinline__ double entropy_root(const Gas &g, const double *u,
                                             const double *P, double b,
                                             double phi_min) {
+#pragma clang fp contract(off)  // the same bits in every kernel
   double a = 0.0;
-  double fa = psi_eval<DIM>(g, u, P, 0.0, phi_min, nullptr);
+  double fa = psi_eval<DIM, SEV>(g, u, P, 0.0, phi_min, nullptr);
   double dfb;
-  double fb = psi_eval<DIM>(g, u, P, b, phi_min, &dfb);
+  double fb = psi_eval<DIM, SEV>(g, u, P, b, phi_min, &dfb);
   if (fa < 0.0) return 0.0;
   if (fb >= 0.0) return b;
   for (int it = 0; it < 24 && b - a > 1e-14; ++it) {
     const double w0 = b - a;
     const double xs = a - fa * (b - a) / (fb - fa);
     if (xs > a && xs < b) {
-      const double f = psi_eval<DIM>(g, u, P, xs, phi_min, nullptr);
+      const double f = psi_eval<DIM, SEV>(g, u, P, xs, phi_min, nullptr);
       if (f >= 0.0) { a = xs; fa = f; }
       else { b = xs; fb = f; dfb = 0.0; }
     }
@@ -210,7 +229,7 @@ __device__ __forceinline__ double entropy_root(const Gas &g, const double *u,
       const double xn = b - fb / dfb;
       if (xn > a && xn < b) {
         double d;
-        const double f = psi_eval<DIM>(g, u, P, xn, phi_min, &d);
+        const double f = psi_eval<DIM, SEV>(g, u, P, xn, phi_min, &d);
         if (f < 0.0) { b = xn; fb = f; dfb = d; }
         else { a = xn; fa = f; }
       }
@@ -218,78 +237,60 @@ __device__ __forceinline__ double entropy_root(const Gas &g, const double *u,
     if (b - a > 0.5 * w0) {
       const double xm = 0.5 * (a + b);
       double d;
-      const double f = psi_eval<DIM>(g, u, P, xm, phi_min, &d);
+      const double f = psi_eval<DIM, SEV>(g, u, P, xm, phi_min, &d);
       if (f >= 0.0) { a = xm; fa = f; }
       else { b = xm; fb = f; dfb = d; }
     }
-    if (dfb == 0.0 && b - a > 1e-14) psi_eval<DIM>(g, u, P, b, phi_min, &dfb);
+    if (dfb == 0.0 && b - a > 1e-14) psi_eval<DIM, SEV>(g, u, P, b, phi_min, &dfb);
   }
   return a;
 }
 
-// Root of the entropy bound for gamma = 7/5 on the polynomial form of the
-// test: g(l) = A(l)^5 - phi_min^5 rho(l)^12 with rho(l) = rho + l P_rho and
-// A(l) = rho(l) E(l) - |m(l)|^2/2 = a0 + a1 l + a2 l^2 (rho(l) eps(l)).  g has
-// the sign of psi wherever rho > 0, so its root in (0, b) is psi's.
-// Safeguarded Newton inside the bracket [a, b] (g(a) >= 0 > g(b)), falling
-// back to bisection when a Newton step leaves the bracket or shrinks it too
-// little; stops at a bracket of 1e-14 and returns the feasible end.  No
-// divisions by state values and no pow: a handful of FMAs per iteration.
+// Root of the entropy bound for gamma = 7/5, to about 1e-9, on the polynomial
+// form of the test: with rho(l) = rho + l P_rho and A(l) = rho(l) E(l) -
+// |m(l)|^2/2 = a0 + a1 l + a2 l^2 (rho(l) eps(l)) the bound holds where
+// q = phi_min^5 rho^12 / A^5 <= 1.  Newton on log q, whose slope changes
+// little over (0, b) (on A^5 - phi_min^5 rho^12, twelfth powers, one lane in
+// a hundred took over 30 steps; here 4, and the slowest lane decides), kept
+// inside the bracket [lo, hi] (q(lo) <= 1 < q(hi)) by bisection.  No division
+// by state values, no pow: some 40 instructions a step.
 template <int DIM>
 __device__ __forceinline__ double entropy_root_seven(const double *u,
                                                     const double *P, double b,
                                                     double pmin5) {
+#pragma clang fp contract(off)  // the same bits in every kernel
   const double r0 = u[0], pr = P[0];
   double m0p = 0.0, pm2 = 0.0, m02 = 0.0;
 #pragma unroll
   for (int k = 0; k < DIM; ++k) {
-    m0p += u[1 + k] * P[1 + k];
-    pm2 += P[1 + k] * P[1 + k];
-    m02 += u[1 + k] * u[1 + k];
+    m0p = fma(u[1 + k], P[1 + k], m0p);
+    pm2 = fma(P[1 + k], P[1 + k], pm2);
+    m02 = fma(u[1 + k], u[1 + k], m02);
   }
   const double E0 = u[DIM + 1], pE = P[DIM + 1];
-  const double a0 = r0 * E0 - 0.5 * m02;
-  const double a1 = r0 * pE + pr * E0 - m0p;
-  const double a2 = pr * pE - 0.5 * pm2;
-  auto g = [&](double l, double *dg) {
-    const double r = r0 + l * pr;
-    const double A = a0 + l * (a1 + l * a2);
-    const double dA = a1 + 2.0 * l * a2;
-    const double A2 = A * A, A4 = A2 * A2;
-    const double r2 = r * r, r4 = r2 * r2, r8 = r4 * r4, r11 = r8 * r2 * r;
-    *dg = 5.0 * A4 * dA - 12.0 * pmin5 * r11 * pr;
-    return A4 * A - pmin5 * (r11 * r);
-  };
-  double a = 0.0, dga, dgb;
-  double ga = g(0.0, &dga);
-  double gb = g(b, &dgb);
-  if (!(ga >= 0.0)) return 0.0;
-  if (gb >= 0.0) return b;
-  // start from the chord's root, then Newton; once a Newton step is below
-  // round-off the bracket is closed with two probes around it
-  double x = a - ga * (b - a) / (gb - ga);
-  if (!(x > a && x < b)) x = 0.5 * (a + b);
-  for (int it = 0; it < 60 && b - a > 1e-14; ++it) {
-    double dgx;
-    const double gx = g(x, &dgx);
-    if (gx >= 0.0) a = x;
-    else b = x;
-    if (b - a <= 1e-14) break;
-    double xn = x - gx / dgx;
-    if (!(xn > a && xn < b)) {
-      xn = 0.5 * (a + b);
-    } else if (fabs(xn - x) < 2e-15) {
-      double d;
-      const double lo = fmax(xn - 4e-15, a), hi = fmin(xn + 4e-15, b);
-      if (g(lo, &d) >= 0.0) a = lo; else b = lo;
-      if (hi > a && hi < b) {
-        if (g(hi, &d) >= 0.0) a = hi; else b = hi;
-      }
-      xn = 0.5 * (a + b);
-    }
-    x = xn;
+  const double a0 = fma(r0, E0, -0.5 * m02);
+  const double a1 = fma(r0, pE, fma(pr, E0, -m0p));
+  const double a2 = fma(pr, pE, -0.5 * pm2);
+  double lo = 0.0, hi = b, x = 0.0;
+  for (int it = 0; it < 40; ++it) {
+    const double r = fma(x, pr, r0);
+    const double A = fma(x, fma(x, a2, a1), a0);
+    const double A2 = A * A;
+    const double r2 = r * r, r4 = r2 * r2, r8 = r4 * r4;
+    const double t = fma(pmin5 * r8 * r4, fast_rcp(A2 * A2 * A), -1.0);  // q - 1
+    if (A > 0.0 && t <= 0.0) lo = x;
+    else hi = x;
+    const double lq = fabs(t) < 0.01
+                          ? t * fma(-t, fma(-t, fma(-t, 0.25, 1.0 / 3.0), 0.5), 1.0)
+                          : 0.6931471805599453 * (double)__builtin_amdgcn_logf((float)(1.0 + t));
+    // d(log q)/dl = 12 rho'/rho - 5 A'/A
+    const double dq = fma(12.0 * pr, A, -5.0 * r * fma(2.0 * x, a2, a1));
+    const double d = -lq * (A * r) * fast_rcp(dq);
+    if (fabs(d) <= 1e-9) return fmin(fmax(x + d, lo), hi);
+    x += d;
+    if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);
   }
-  return a;
+  return x;
 }
 
 // Root of the entropy bound to the accuracy of psi itself.  For gamma = 7/5
@@ -305,22 +306,23 @@ template <int DIM, int SEV>
 __device__ __forceinline__ double entropy_root_fast(const Gas &g, const double *u,
                                                    const double *P, double lr,
                                                    double pmin, double pmin5) {
+#pragma clang fp contract(off)  // the same bits in every kernel
   if constexpr (SEV) {
     const double x = entropy_root_seven<DIM>(u, P, lr, pmin5);
     double d;
-    const double f = psi_eval<DIM>(g, u, P, x, pmin, &d);
+    const double f = psi_eval<DIM, SEV>(g, u, P, x, pmin, &d);
     if (d < 0.0) {
       const double x1 = x - f / d;
       if (x1 > 0.0 && x1 <= lr) {
         double h = 2e-15;
         for (int k = 0; k < 4; ++k, h *= 8.0) {
           const double a = fmax(x1 - h, 0.0);
-          if (psi_eval<DIM>(g, u, P, a, pmin, nullptr) >= 0.0) return a;
+          if (psi_eval<DIM, SEV>(g, u, P, a, pmin, nullptr) >= 0.0) return a;
         }
       }
     }
   }
-  return entropy_root<DIM>(g, u, P, lr, pmin);
+  return entropy_root<DIM, SEV>(g, u, P, lr, pmin);
 }
 
 }  // namespace ns

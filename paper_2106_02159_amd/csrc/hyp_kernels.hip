@@ -962,7 +962,6 @@ __device__ __forceinline__ void clear_lists(const StageArgsT<LT> &A, bool first)
   if (first) {
     A.qcnt[0] = 0;
     A.qcnt[1] = 0;
-    if (A.drow) A.qcnt[2] = 0;
   }
 }
 
@@ -1276,7 +1275,7 @@ __device__ __forceinline__ void gather_P(const DevGraphT<LT> &G, const StageArgs
 template <int DIM>
 __device__ __forceinline__ void make_P(const RowCtx<DIM> &R, const PIn<DIM> &x,
                                        double *P) {
-#pragma clang fp contract(off)  // the same bits in every kernel (k_lim2 MODE 4)
+#pragma clang fp contract(off)  // the same bits in every kernel
   constexpr int NC = DIM + 2;
   const double dH = 0.5 * (R.ali + x.al) * x.d;
 #pragma unroll
@@ -1320,18 +1319,21 @@ struct Bounds {
   double rmin, rmax, pmin, pmin5;
 };
 
-template <typename LT>
-__device__ __forceinline__ Bounds load_bounds(const StageArgsT<LT> &A, int64_t N,
-                                              int64_t i) {
+__device__ __forceinline__ Bounds make_bounds(const double *bv) {
   Bounds b;
-  double bv[3];
-  load_state<3>(A.bnds, N, i, bv);  // (rho_min, rho_max) in one load
   b.rmin = bv[0];
   b.rmax = bv[1];
   b.pmin = bv[2];
   const double p2 = b.pmin * b.pmin;
   b.pmin5 = p2 * p2 * b.pmin;
   return b;
+}
+template <typename LT>
+__device__ __forceinline__ Bounds load_bounds(const StageArgsT<LT> &A, int64_t N,
+                                              int64_t i) {
+  double bv[3];
+  load_state<3>(A.bnds, N, i, bv);  // (rho_min, rho_max) in one load
+  return make_bounds(bv);
 }
 
 // Limiter line search for every off-diagonal entry of the row.  The cheap
@@ -1345,11 +1347,9 @@ template <int DIM, int SEV>
 __device__ __forceinline__ int limit_fast(const Gas &g, const double *u,
                                           const double *P, const Bounds &b,
                                           double *l) {
-#pragma clang fp contract(off)  // the same bits in every kernel (k_lim2 MODE 4)
-  double lr;
-  if (P[0] > 0.0) lr = (b.rmax - u[0]) / P[0];
-  else if (P[0] < 0.0) lr = (b.rmin - u[0]) / P[0];
-  else lr = 1.0;
+#pragma clang fp contract(off)  // the same bits in every kernel
+  double lr = ((P[0] > 0.0 ? b.rmax : b.rmin) - u[0]) / P[0];
+  if (!(P[0] > 0.0 || P[0] < 0.0)) lr = 1.0;
   lr = fmin(fmax(lr, 0.0), 1.0);
   *l = lr;
   if (entropy_ok<DIM, SEV>(g, u, P, lr, b.pmin, b.pmin5)) return 0;
@@ -1360,7 +1360,7 @@ __device__ __forceinline__ int limit_fast(const Gas &g, const double *u,
 template <int DIM, int SEV, typename LT>
 __device__ __forceinline__ void lim1_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                          const Gas &g, uint32_t blk, int64_t i) {
-#pragma clang fp contract(off)  // the same bits as k_lim2 MODE 4
+#pragma clang fp contract(off)  // the same bits in every kernel
   using C = Cfg<DIM, NS_CH_LIM1>;
   constexpr int NC = C::NC;
   const int64_t N = G.N;
@@ -1410,27 +1410,15 @@ __global__ __launch_bounds__(kBlock) void k_lim1(DevGraphT<LT> G, StageArgsT<LT>
   lim1_row<DIM, SEV, LT>(G, A, g, blockIdx.x, row_id());
 }
 
-// MODE 0: convex, pass-1 update + pass-2 line search; 1: convex with one
-// pass, final; 2: l = 1 (unlimited high order), final; 3: convex, pass-1
-// update only (3D: the pass-2 search is k_lim2b, since both in one kernel
-// need more registers than a SIMD lane has); 4: MODE 0 with the pass-1 line
-// searches in the same sweep (2D, replaces k_lim1).
-//
-// MODE 4: for every entry the row runs both line searches of the pair --
-// its own on P_ij from its U^L and bounds, and the neighbour's on P_ji from
-// the neighbour's, with P_ji formed from the same operands in the same
-// order as the neighbour's row forms it -- so the two rows obtain the same
-// l_ij = min(l~_ij, l~_ji) without a sweep storing l~ in between.  The own
-// search is still stored in lt1 (a deferred neighbour reads it).  Where
-// either search of a pair needs the root of the entropy bound, both rows of
-// the pair are deferred: the own entries go to the pass-1 work list as in
-// k_lim1, the row to the deferred list, and k_lim2_rows completes it with
-// MODE 0 once k_root has solved the list.
+// MODE 0: convex, pass-1 update + pass-2 line search (2D, the persistent
+// steps); 1: convex with one pass, final; 2: l = 1 (unlimited high order),
+// final; 3: convex, pass-1 update only (3D: the pass-2 search is k_lim2b,
+// since both in one kernel need more registers than a SIMD lane has).
 template <int DIM, int MODE, int SEV, typename LT>
 __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                          const Gas &g, uint32_t blk, int64_t i) {
-  // no fused multiply-adds of the compiler's choosing: MODE 0 and MODE 4
-  // must give the same bits (the persistent steps run MODE 0 throughout)
+  // no fused multiply-adds of the compiler's choosing: MODE 0 must give the
+  // bits of the launch path's kernels
 #pragma clang fp contract(off)
   using C = Cfg<DIM, NS_CH_LIM2>;
   constexpr int NC = C::NC;
@@ -1444,20 +1432,10 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
   const double lam = 1.0 / G.lfac[i];
   double u1[NC];
   load_state<NC>(A.UL, N, i, u1);
-  constexpr bool BOTH = MODE == 4;  // both pass-1 searches of every pair here
-  double ul[BOTH ? NC : 1];
-  Bounds bi{};
-  uint32_t slow1 = 0;
-  bool defer = false;
-  if constexpr (BOTH) {
-#pragma unroll
-    for (int q = 0; q < NC; ++q) ul[q] = u1[q];
-    bi = load_bounds(A, N, i);
-  }
   // 2D: the row's P_ij and l_ij stay for the pass-2 search: the P of the
   // first NS_LIM2_LDS off-diagonal slots in the lane's own LDS words (no
   // sharing between lanes, so no barrier), the rest in registers
-  constexpr bool CACHE = DIM == 2 && (MODE == 0 || MODE == 4);
+  constexpr bool CACHE = DIM == 2 && MODE == 0;
   constexpr int NLDS = CACHE ? NS_LIM2_LDS : 0;
   __shared__ double Ps[NLDS > 0 ? NLDS : 1][NC][kBlock];
   const int lane = threadIdx.x;
@@ -1469,8 +1447,6 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
     if constexpr (!CACHE) colk.fence();
     PIn<DIM> x[C::CH];
     double la[C::CH], lb[C::CH];
-    double ulj[BOTH ? C::CH : 1][NC], cj[C::CH];
-    Bounds bj[BOTH ? C::CH : 1];
     int32_t jc[C::CH];
 #pragma unroll
     for (int kk = 0; kk < C::CH; ++kk) {
@@ -1480,11 +1456,7 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
       if (k == C::W / 2) continue;  // the diagonal has no P
       const int64_t js = jc[kk] >= 0 ? jc[kk] : i;
       gather_P<DIM>(G, A, e, js, colk.mass(k), x[kk]);
-      if constexpr (BOTH) {
-        load_state<NC>(A.UL, N, js, ulj[kk]);
-        bj[kk] = load_bounds(A, N, js);
-        cj[kk] = tau * G.crm[js];  // as load_row forms it
-      } else if constexpr (MODE != 2) {
+      if constexpr (MODE != 2) {
         la[kk] = lt1[e];
         lb[kk] = lt1[eidx<DIM>(tslot<DIM>(k), js)];
       }
@@ -1495,37 +1467,7 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
       if (jc[kk] < 0 || jc[kk] == i) continue;
       double P[NC];
       make_P<DIM>(R, x[kk], P);
-      double l;
-      if constexpr (BOTH) {
-        double l1, l2;
-        if (limit_fast<DIM, SEV>(g, ul, P, bi, &l1)) {
-          slow1 |= 1u << k;
-          defer = true;
-        }
-        st_once(&A.lt1[eidx<DIM>(k, i)], to_lt_down<LT>(l1));
-        // the neighbour's search on P_ji, formed as its row forms it
-        RowCtx<DIM> Rj;
-        PIn<DIM> xi;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          Rj.ui[q] = x[kk].u[q];
-          Rj.fi[q] = x[kk].f[q];
-          xi.u[q] = R.ui[q];
-          xi.f[q] = R.fi[q];
-        }
-        Rj.ali = x[kk].al;
-        Rj.coef = cj[kk];
-        xi.al = R.ali;
-        xi.d = x[kk].d;
-        xi.m = x[kk].m;
-        double Pj[NC];
-        make_P<DIM>(Rj, xi, Pj);
-        if (limit_fast<DIM, SEV>(g, ulj[kk], Pj, bj[kk], &l2)) defer = true;
-        // as stored and reloaded by the two-sweep form
-        l = fmin((double)to_lt_down<LT>(l1), (double)to_lt_down<LT>(l2));
-      } else {
-        l = MODE != 2 ? fmin(la[kk], lb[kk]) : 1.0;
-      }
+      const double l = MODE != 2 ? fmin(la[kk], lb[kk]) : 1.0;
 #pragma unroll
       for (int q = 0; q < NC; ++q) u1[q] += lam * l * P[q];
       if constexpr (CACHE) {
@@ -1541,27 +1483,13 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
       }
     }
   }
-  if constexpr (BOTH) {
-    if (slow1) {
-      uint32_t t = atomicAdd(&A.qcnt[0], (uint32_t)__builtin_popcount(slow1));
-      while (slow1) {
-        const int k = __builtin_ctz(slow1);
-        slow1 &= slow1 - 1;
-        A.q[t++] = (uint32_t)eidx<DIM>(k, i);
-      }
-    }
-    if (defer) {
-      A.drow[atomicAdd(&A.qcnt[2], 1u)] = (uint32_t)i;
-      return;
-    }
-  }
   if constexpr (MODE == 3) {
     store_state<NC>(A.U1, N, i, u1);
   } else if constexpr (MODE == 1 || MODE == 2) {
     finish<DIM>(G, A, i, u1);
   } else {
     store_state<NC>(A.U1, N, i, u1);
-    const Bounds b = BOTH ? bi : load_bounds(A, N, i);
+    const Bounds b = load_bounds(A, N, i);
     LT *__restrict__ lt2 = A.lt2;
     uint32_t slow = 0;
     uint32_t nzm = 0;  // slots whose stored product may be nonzero (k_fin)
@@ -1649,15 +1577,488 @@ __global__ __launch_bounds__(kBlock) void k_lim2(DevGraphT<LT> G, StageArgsT<LT>
   lim2_row<DIM, MODE, SEV, LT>(G, A, g, blockIdx.x, row_id());
 }
 
-// The rows that MODE 4 deferred (A.drow, qcnt[2] of them), completed with
-// MODE 0 after k_root<1>; grid-stride over the list.
+// ---------------------------------------------------------------------------
+// 2D, two passes (launch path).  Away from shocks the whole of P_ij passes
+// both searches of every pair of a row: l_ij = 1, nothing is left for pass 2,
+// and the row's result is U^L + lambda_i sum_j P_ij.  So
+//   k_lim_first   sweeps along stencil lines: forms every P_ij, tests whether
+//                 the row's own search returns 1 (no division: only whether
+//                 the step to l = 1 stays inside the bounds), stores that sum
+//                 and a mask of the slots where it does not;
+//   k_lim_done    finishes the rows whose own and neighbours' masks are clear,
+//                 and marks the others (one bit per row);
+//   k_lim_rows    runs both limiter passes, roots included, for the marked
+//                 rows, 8 lanes (the 8 pairs) to a row;
+//   k_fin_rows    adds the pass-2 part of those that have one, 8 lanes to a
+//                 row again.
+// Marked rows come in long runs (a front along x marks whole lines), so a
+// workgroup of k_lim_rows takes slices of 64 rows that lie apart; a wave that
+// worked through its own slice had up to 8 rounds of 8 rows, 13 us each.
+// Against one sweep that gathered every neighbour slot by slot, kept P for
+// pass 2, and listed the entries with a root for two further kernels (FP64,
+// limiter and final update of a stage): 2.61 -> 1.79 ms at 4096^2, 0.27 ->
+// 0.13 ms at 1001 x 1003, 0.11 -> 0.06 ms at 256^2; there the appends to the
+// lists, serial at their counters (15 ns each), and one lane's row of 8
+// searches took the time.  k_lim_first is bound by the latency of its line
+// loads at 4 waves per SIMD (0.80 ms at 4096^2, 245 B per node: 5.1 TB/s),
+// k_lim_done by memory bandwidth (0.27 ms), k_lim_rows by the root finder's
+// dependent chain.
+// Both searches of a pair are evaluated where a row needs them, on operands
+// in the order the other row uses, so that both rows obtain the same l_ij
+// (as for every kernel here, without fused multiply-adds of the compiler's
+// choosing).  KEEP: also store l~, l~' of all entries and U^(1) of all rows
+// (the last stage of a step: ns_stats and ns_get_debug read them).
+
+// Does the line search of u + l P return exactly 1?  (x / y >= 1 if and only
+// if x >= y for y > 0, also rounded.)
+template <int DIM, int SEV>
+__device__ __forceinline__ bool limit_is_one(const Gas &g, const double *u, const double *P,
+                                             const Bounds &b) {
+#pragma clang fp contract(off)
+  const bool rho = P[0] > 0.0 ? b.rmax - u[0] >= P[0] : !(P[0] < 0.0) || b.rmin - u[0] <= P[0];
+  return entropy_ok<DIM, SEV>(g, u, P, 1.0, b.pmin, b.pmin5) && rho;
+}
+
+constexpr uint32_t kSpecRow = 0x80000000u;  // bit of A.lim: a listed row
+constexpr int kWide = 512;                  // lanes: 64 rows of 8 pairs
+
+template <int DIM, int SEV, bool KEEP, typename LT>
+__device__ __forceinline__ void lim_first_lines(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                                const Gas &g, uint32_t blk) {
+#pragma clang fp contract(off)
+  constexpr int NC = DIM + 2, W = Cfg<DIM>::W;
+  const int64_t N = G.N, r0 = (int64_t)blk * kBlock;
+  uint32_t tid = threadIdx.x;
+  const uint32_t lane = tid & 63;
+  const BoxGeom *geo = block_geo(G, blk);
+  const int64_t n0 = geo_ld(&geo->n[0]), n01 = n0 * geo_ld(&geo->n[1]);
+  const bool act = line_row(G, r0 + tid);
+  const bool edge = ((lane + 1) & 63) < 2;  // lanes 63 and 0
+  const LT *__restrict__ dd = A.d;
+  const Line own = make_line(r0, 0, N, tid);
+  RowCtx<DIM> R;
+  line_state<NC>(A.U, N, own.b, own.c, R.ui);
+  line_state<NC>(A.FH, N, own.b, own.c, R.fi);
+  R.ali = line_ld(A.alpha, own.b, own.c);
+  R.coef = A.tau[A.seg ? geo_ld(&A.seg[blk]) : 0] * line_ld(G.crm, own.b, own.c);
+  double ul[NC], u1[NC];
+  line_state<NC>(A.UL, N, own.b, own.c, ul);
+  Bounds b;
+  {
+    double bv[3];
+    line_state<3>(A.bnds, N, own.b, own.c, bv);
+    b = make_bounds(bv);
+  }
+#pragma unroll
+  for (int q = 0; q < NC; ++q) u1[q] = ul[q];
+  constexpr double lam = 1.0 / (W - 1);
+  uint32_t mask = 0;
+  const uint32_t e0 = min((tid >> 6), (uint32_t)((N - 1 - r0) >> 6)) * (W * 64) + lane;
+  static_for<0, W / 3>([&](auto line) __attribute__((always_inline)) {
+    constexpr int ln = decltype(line)::value;
+    constexpr int dy = ln % 3 - 1, dz = DIM == 3 ? ln / 3 - 1 : 0;
+    constexpr bool self = dy == 0 && dz == 0;
+    line_fence(tid);
+    const Line L = make_line(r0, dy * n0 + dz * n01, N, tid);
+    double uc[NC], uh[NC], fc[NC], fh[NC], ac, ah = 0.0, dk[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (3 * ln + t != W / 2) dk[t] = ld_once<LT>(edge_at<DIM>(dd, r0, 3 * ln + t, e0));
+#pragma unroll
+    for (int q = 0; q < NC; ++q) uh[q] = fh[q] = 0.0;
+    if (self) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) { uc[q] = R.ui[q]; fc[q] = R.fi[q]; }
+      ac = R.ali;
+    } else {
+      line_state<NC>(A.U, N, L.b, L.c, uc);
+      line_state<NC>(A.FH, N, L.b, L.c, fc);
+      ac = line_ld(A.alpha, L.b, L.c);
+    }
+    if (edge) {
+      line_state<NC>(A.U, N, L.b, L.h, uh);
+      line_state<NC>(A.FH, N, L.b, L.h, fh);
+      ah = line_ld(A.alpha, L.b, L.h);
+    }
+    static_for<0, 3>([&](auto along) __attribute__((always_inline)) {
+      constexpr int dx = decltype(along)::value - 1;
+      if constexpr (self && dx == 0) return;  // the diagonal has no P
+      constexpr int k = 3 * ln + dx + 1, cls = slot_class<DIM>(k);
+      PIn<DIM> x;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        x.u[q] = dx == 0 ? uc[q] : side(dx, uh[q], uc[q]);
+        x.f[q] = dx == 0 ? fc[q] : side(dx, fh[q], fc[q]);
+      }
+      x.al = dx == 0 ? ac : side(dx, ah, ac);
+      x.d = dk[dx + 1];
+      x.m = geo_ld(&geo->im[cls]);
+      double P[NC];
+      make_P<DIM>(R, x, P);
+      const bool one = limit_is_one<DIM, SEV>(g, ul, P, b);
+      mask |= one ? 0u : 1u << k;
+      if constexpr (KEEP)
+        if (act) {
+          st_once<LT>(edge_at<DIM>(A.lt1, r0, k, e0), LT(1));
+          st_once<LT>(edge_at<DIM>(A.lt2, r0, k, e0), LT(0));
+        }
+#pragma unroll
+      for (int q = 0; q < NC; ++q) u1[q] += lam * P[q];
+    });
+#pragma unroll
+    for (int q = 0; q < NC; ++q) line_keep(u1[q]);
+    line_keep(mask);
+  });
+  if (act) {
+    store_state<NC>(A.U1, N, r0 + tid, u1);
+    A.lim[r0 + tid] = mask;
+  }
+}
+
+// P_ij of an entry and P_ji as row j forms it: the bracket of P_ji is that
+// of P_ij with the sign changed, exactly.
+template <int DIM>
+__device__ __forceinline__ void make_P_both(const RowCtx<DIM> &R, const PIn<DIM> &x, double cj,
+                                            double *P, double *Pj) {
+#pragma clang fp contract(off)
+  const double dH = 0.5 * (R.ali + x.al) * x.d;
+#pragma unroll
+  for (int q = 0; q < DIM + 2; ++q) {
+    const double B = x.m * (R.fi[q] - x.f[q]) + (dH - x.d) * (x.u[q] - R.ui[q]);
+    P[q] = R.coef * B;
+    Pj[q] = cj * -B;
+  }
+}
+
+// A listed row's mask: the own searches, one lane per line.
 template <int DIM, int SEV, typename LT>
-__global__ __launch_bounds__(kBlock) void k_lim2_rows(DevGraphT<LT> G, StageArgsT<LT> A,
-                                                      Gas g) {
-  const uint32_t n = A.qcnt[2];
-  for (uint32_t t = blockIdx.x * kBlock + threadIdx.x; t < n; t += gridDim.x * kBlock) {
-    const int64_t i = A.drow[t];
-    lim2_row<DIM, 0, SEV, LT>(G, A, g, (uint32_t)(i / kBlock), i);
+__device__ __forceinline__ void lim_first_spec(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                               const Gas &g) {
+  constexpr int NC = DIM + 2;
+  const SpecLane<DIM> L(G);
+  const int64_t N = G.N, i = L.i;
+  const BoxNbr<DIM> jv = row_nbr<DIM>(G, i);
+  RowCtx<DIM> R;
+  load_row<DIM>(G, A, i, A.tau[member(A, i)], R);
+  double ul[NC];
+  load_state<NC>(A.UL, N, i, ul);
+  const Bounds b = load_bounds(A, N, i);
+  uint32_t mask = 0;
+#pragma unroll 1
+  for (int t = 0; t < 3; ++t) {
+    const int k = 3 * L.line + t;
+    const int32_t j = jv[k];
+    PIn<DIM> x;
+    gather_P<DIM>(G, A, eidx<DIM>(k, i), j >= 0 ? j : i, jv.mass(k), x);
+    double P[NC];
+    make_P<DIM>(R, x, P);
+    if (j >= 0 && j != i && !limit_is_one<DIM, SEV>(g, ul, P, b)) mask |= 1u << k;
+  }
+#pragma unroll
+  for (int l = 1; l < SpecLane<DIM>::NL; ++l) mask |= __shfl(mask, min(L.base + l, 63));
+  if (L.ok && L.line == 0) A.lim[i] = mask | kSpecRow;
+}
+
+template <int DIM, int SEV, bool KEEP, typename LT>
+__global__ __launch_bounds__(kBlock) void k_lim_first(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
+  const uint32_t ns = spec_blocks<DIM>(G);
+  if (blockIdx.x < ns) lim_first_spec<DIM, SEV, LT>(G, A, g);
+  else lim_first_lines<DIM, SEV, KEEP, LT>(G, A, g, blockIdx.x - ns);
+}
+
+// Both passes of one 2D row by the 8 lanes at `base`: lane o has the o-th
+// off-diagonal slot.  Every lane of the wave calls it; lanes with ok = false
+// repeat a row without stores.
+template <int SEV, bool KEEP, typename LT>
+__device__ __forceinline__ void lim_pairs(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                          const Gas &g, int64_t i, int o, int base, bool ok,
+                                          uint32_t *roots, double *nb_words) {
+#pragma clang fp contract(off)
+  constexpr int NC = 4;
+  const int64_t N = G.N;
+  const BoxNbr<2> nb = row_nbr<2>(G, i);
+  const int k = o < 4 ? o : o + 1;
+  const int32_t j = nb[k];
+  const bool there = j >= 0;
+  const int64_t js = there ? j : i, e = eidx<2>(k, i);
+  const double tau = A.tau[member(A, i)];
+  RowCtx<2> R;
+  PIn<2> x;
+  load_row<2>(G, A, i, tau, R);
+  gather_P<2>(G, A, e, js, nb.mass(k), x);
+  double ul[NC], uj[NC], P[NC], Pj[NC];
+  load_state<NC>(A.UL, N, i, ul);
+  load_state<NC>(A.UL, N, js, uj);
+  const Bounds b = load_bounds(A, N, i), bj = load_bounds(A, N, js);
+  make_P_both<2>(R, x, tau * G.crm[js], P, Pj);
+  const double lam = 1.0 / G.lfac[i];
+  // Pass 1: the pair's two searches; pass 2: the search on (1 - l) P from the
+  // updated row.  `pend`: a bit for each search that needs the root (0 own,
+  // 1 neighbour's, 2 pass 2).  The root finder is one body and runs for every
+  // lane's next one at once: few pairs have two.  The neighbour's operands
+  // wait in the lane's LDS words (in registers they were spilled inside the
+  // root finder's loops).
+  double l = 1.0, s1 = 1.0, u1[NC], own = 1.0, rj = 1.0, l2 = 0.0;
+  uint32_t pend = 0;
+  if (there && limit_fast<2, SEV>(g, uj, Pj, bj, &rj)) {
+    pend = 2;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      nb_words[q * kWide] = uj[q];
+      nb_words[(NC + q) * kWide] = Pj[q];
+    }
+    nb_words[2 * NC * kWide] = bj.pmin;
+  }
+  bool slow1 = false, slow2 = false;
+#pragma unroll
+  for (int q = 0; q < NC; ++q) u1[q] = ul[q];
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    double r0 = pass ? 0.0 : 1.0;
+    if (there && s1 != 0.0 && limit_fast<2, SEV>(g, u1, P, b, &r0)) pend |= 1;
+    if (pass) slow2 = pend & 1;
+    else slow1 = pend & 1;
+#pragma unroll 1
+    while (__any(pend)) {
+      const bool nbr = pend == 2;
+      double us[NC], Ps[NC], pm = b.pmin;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        us[q] = u1[q];
+        Ps[q] = P[q];
+      }
+      if (nbr) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          us[q] = nb_words[q * kWide];
+          Ps[q] = nb_words[(NC + q) * kWide];
+        }
+        pm = nb_words[2 * NC * kWide];
+      }
+      if (pend) {
+        const double p2 = pm * pm;
+        const double r = entropy_root_fast<2, SEV>(g, us, Ps, nbr ? rj : r0, pm, p2 * p2 * pm);
+        if (nbr) rj = r;
+        else r0 = r;
+        pend &= pend - 1;
+      }
+    }
+    if (pass == 0) {
+      own = (double)to_lt_down<LT>(r0);
+      l = fmin(own, (double)to_lt_down<LT>(rj));
+      s1 = 1.0 - l;  // (0: the stored product is 0)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const double t = there ? lam * l * P[q] : 0.0;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) u1[q] += __shfl(t, base + p);  // in slot order
+        P[q] *= s1;
+      }
+    } else {
+      l2 = r0 * s1;
+    }
+  }
+  const LT sv = to_lt_down<LT>(l2);
+  if (ok && there) {
+    if constexpr (KEEP) A.lt1[e] = (LT)own;
+    if (KEEP || sv != LT(0)) A.lt2[e] = sv;
+  }
+  const uint64_t nzw = __ballot(ok && there && sv != LT(0));
+  const uint32_t m8 = (uint32_t)(nzw >> base) & 0xffu, nz = (m8 & 15u) | (m8 >> 4) << 5;
+  if constexpr (KEEP) {  // entries that needed the root finder
+    const int n1 = __builtin_popcountll(__ballot(ok && slow1));
+    const int n2 = __builtin_popcountll(__ballot(ok && slow2));
+    if ((threadIdx.x & 63) == 0 && (n1 | n2)) {
+      atomicAdd(&roots[0], (uint32_t)n1);
+      atomicAdd(&roots[1], (uint32_t)n2);
+    }
+  }
+  if (ok && o == 0) {
+    A.nzm[i] = nz;
+    if (KEEP || nz) store_state<NC>(A.U1, N, i, u1);
+    if (!nz) finish<2>(G, A, i, u1);
+  }
+}
+
+// Finishes the interior rows without a limited pair; A.todo: the others, a
+// bit each per slice of 64 rows.
+template <typename LT>
+__global__ __launch_bounds__(kBlock) void k_lim_done(DevGraphT<LT> G, StageArgsT<LT> A) {
+  const int64_t N = G.N, r0 = (int64_t)blockIdx.x * kBlock;
+  const uint32_t tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int64_t n0 = geo_ld(&block_geo(G, blockIdx.x)->n[0]);
+  const bool act = line_row(G, r0 + tid);
+  const bool edge = ((lane + 1) & 63) < 2;
+  uint32_t mc[3], mh[3] = {0, 0, 0};
+#pragma unroll
+  for (int ln = 0; ln < 3; ++ln) {
+    const Line L = make_line(r0, (ln - 1) * n0, N, tid);
+    mc[ln] = line_ld(A.lim, L.b, L.c);
+    if (edge) mh[ln] = line_ld(A.lim, L.b, L.h);
+  }
+  double u1[4];
+  const Line own = make_line(r0, 0, N, tid);
+  line_state<4>(A.U1, N, own.b, own.c, u1);
+  uint32_t lim = mc[1];
+#pragma unroll
+  for (int ln = 0; ln < 3; ++ln) {
+    // slot k of this row is slot 8 - k of the neighbour's
+    lim |= (from_left(mh[ln], mc[ln]) >> (8 - 3 * ln)) & 1u;
+    if (ln != 1) lim |= (mc[ln] >> (7 - 3 * ln)) & 1u;
+    lim |= (from_right(mh[ln], mc[ln]) >> (6 - 3 * ln)) & 1u;
+  }
+  if (act) {
+    A.nzm[r0 + tid] = 0;
+    if (lim == 0) finish<2>(G, A, r0 + tid, u1);
+  }
+  const uint64_t todo = __ballot(act && lim != 0);
+  if (lane == 0 && r0 + tid < N) A.todo[(r0 + tid) >> 6] = todo;
+}
+
+// Workgroups of k_lim_rows beside those of the listed rows: two per CU (what
+// fits), or as many as keep each at 128 slices (b, b + n, b + 2n, ...).
+constexpr int kSlices = 128;
+__host__ __device__ __forceinline__ uint32_t lim_groups(int64_t N) {
+  const int64_t sl = (N + 63) / 64, n = (sl + kSlices - 1) / kSlices;
+  return (uint32_t)(n > 512 ? n : sl < 512 ? sl : 512);
+}
+__host__ __device__ __forceinline__ uint32_t lim_slices(int64_t N) {
+  const uint32_t n = lim_groups(N);
+  return (uint32_t)(((N + 63) / 64 + n - 1) / n);
+}
+__host__ __device__ __forceinline__ uint32_t spec_groups(int nsrow) {
+  return (uint32_t)(nsrow + 63) / 64;
+}
+
+// The listed rows (front workgroups), and the marked rows of the workgroup's
+// slices, 64 rows at a time.  Their list goes to A.q for k_fin_rows, its
+// length to A.q2.
+template <int SEV, bool KEEP, typename LT>
+__global__ __launch_bounds__(kWide) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_lim_rows(
+    DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
+  __shared__ double nb_words[9][kWide];
+  __shared__ uint32_t list[kSlices * 64];
+  __shared__ uint64_t bits[kSlices];
+  __shared__ uint32_t first[kSlices + 1], roots[2];
+  const uint32_t ns = spec_groups(G.nsrow), tid = threadIdx.x;
+  const uint32_t lane = tid & 63, wave = tid >> 6;
+  const bool front = blockIdx.x < ns;
+  uint32_t n = 64;
+  if (KEEP && tid < 2) roots[tid] = 0;
+  if (front) {
+    if (tid < 64) list[tid] = G.srow[min((int)(blockIdx.x * 64 + tid), G.nsrow - 1)];
+    n = min(64u, (uint32_t)G.nsrow - blockIdx.x * 64);
+    __syncthreads();
+  } else {
+    const uint32_t b = blockIdx.x - ns, stride = lim_groups(G.N), most = lim_slices(G.N);
+    const uint32_t slices = (uint32_t)((G.N + 63) / 64);
+    if (wave == 0) {  // bits and running counts of the slices
+      uint32_t sum = 0;
+#pragma unroll
+      for (uint32_t t0 = 0; t0 < kSlices; t0 += 64) {
+        const uint32_t t = t0 + lane, sl = b + t * stride;
+        const uint64_t w = t < most && sl < slices ? A.todo[sl] : 0;
+        uint32_t c = (uint32_t)__builtin_popcountll(w);
+        const uint32_t own = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const uint32_t o = __shfl_up(c, d);
+          if ((int)lane >= d) c += o;
+        }
+        bits[t] = w;
+        first[t] = sum + c - own;
+        sum += __shfl(c, 63);
+      }
+      if (lane == 0) {
+        first[kSlices] = sum;
+        A.q2[b] = sum;
+      }
+    }
+    __syncthreads();
+    n = first[kSlices];
+    for (uint32_t t = wave; t < most; t += kWide / 64) {
+      const uint64_t w = bits[t];
+      if ((w >> lane) & 1u) {
+        const uint32_t at = first[t] + __builtin_amdgcn_mbcnt_hi(
+                                (uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0));
+        const uint32_t row = (b + t * stride) * 64 + lane;
+        list[at] = row;
+        A.q[b * (most * 64) + at] = row;
+      }
+    }
+    __syncthreads();
+  }
+  for (uint32_t t0 = 0; t0 < n; t0 += 64) {
+    const uint32_t t = t0 + (tid >> 3);
+    lim_pairs<SEV, KEEP, LT>(G, A, g, list[min(t, n - 1)], lane & 7, lane & ~7u, t < n,
+                              roots, &nb_words[0][tid]);
+  }
+  if constexpr (KEEP) {
+    __syncthreads();
+    if (tid < 2) A.q2[lim_groups(G.N) + 2 * blockIdx.x + tid] = roots[tid];
+  }
+}
+
+// U = U^(1) + lambda_i sum l' (1 - l) P of a limited row with a pass-2 part,
+// by the 8 lanes at `base` (see lim_pairs), in slot order.  A product that
+// its row did not store is 0 (its mask bit is clear).
+template <typename LT>
+__device__ __forceinline__ void fin_pairs(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                          int64_t i, int o, int base, bool ok) {
+#pragma clang fp contract(off)
+  constexpr int NC = 4;
+  const int64_t N = G.N;
+  const int k = o < 4 ? o : o + 1;
+  const uint32_t nz = A.nzm[i];
+  ok = ok && nz != 0;
+  double t[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) t[q] = 0.0;
+  if (ok && ((nz >> k) & 1u)) {
+    const BoxNbr<2> jv = row_nbr<2>(G, i);
+    const int32_t j = jv[k];
+    const int64_t e = eidx<2>(k, i), et = eidx<2>(tslot<2>(k), j);
+    const double la = A.lt2[e], lb = A.lt2[et];
+    RowCtx<2> R;
+    load_row<2>(G, A, i, A.tau[member(A, i)], R);
+    PIn<2> x;
+    gather_P<2>(G, A, e, j, jv.mass(k), x);
+    const double w = (A.nzm[j] >> tslot<2>(k)) & 1u ? 1.0 / G.lfac[i] * fmin(la, lb) : 0.0;
+    double P[NC];
+    make_P<2>(R, x, P);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) t[q] = w * P[q];
+  }
+  double u2[NC];
+  load_state<NC>(A.U1, N, i, u2);
+#pragma unroll
+  for (int q = 0; q < NC; ++q)
+#pragma unroll
+    for (int p = 0; p < 8; ++p) u2[q] += __shfl(t[q], base + p);
+  if (ok && o == 0) finish<2>(G, A, i, u2);
+}
+
+template <typename LT>
+__global__ __launch_bounds__(kWide) void k_fin_rows(DevGraphT<LT> G, StageArgsT<LT> A) {
+  const uint32_t ns = spec_groups(G.nsrow), tid = threadIdx.x;
+  const int lane = tid & 63;
+  if (A.keep && blockIdx.x == 0 && tid < 128) {
+    // root entries of both passes: wave p sums pass p + 1's counts
+    const uint32_t p = tid >> 6;
+    uint32_t c = 0;
+    for (uint32_t t = lane; t < gridDim.x; t += 64) c += A.q2[lim_groups(G.N) + 2 * t + p];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
+    if (lane == 0) A.qcnt[p] = c;
+  }
+  const bool front = blockIdx.x < ns;
+  const uint32_t b = front ? blockIdx.x : blockIdx.x - ns;
+  const uint32_t n = front ? min(64u, (uint32_t)G.nsrow - b * 64) : A.q2[b];
+  const uint32_t first = b * (front ? 64u : lim_slices(G.N) * 64);
+  for (uint32_t t0 = 0; t0 < n; t0 += 64) {
+    const uint32_t t = t0 + (tid >> 3), at = first + min(t, n - 1);
+    fin_pairs<LT>(G, A, front ? (uint32_t)G.srow[at] : A.q[at], lane & 7, lane & ~7, t < n);
   }
 }
 
@@ -1791,6 +2192,7 @@ __global__ __launch_bounds__(kBlock) void k_root(DevGraphT<LT> G, StageArgsT<LT>
 template <int DIM, typename LT>
 __device__ __forceinline__ void fin_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                         const Gas &g, uint32_t blk, int64_t i) {
+#pragma clang fp contract(off)  // the same bits in every kernel
   using C = Cfg<DIM, NS_CH_FIN>;
   constexpr int NC = C::NC;
   const int64_t N = G.N;
@@ -2305,7 +2707,6 @@ __global__ __launch_bounds__(kBlock) void k_persist(DevGraphT<LT> G, PersistArgs
     // the member's own work lists: its slice of q and its two counters
     A.q = P.A.q + (int64_t)W * kBlock * mb0;
     A.q2 = A.q;  // root1 empties the list before lim2 fills it again
-    A.drow = nullptr;
     A.qcnt = P.pcnt + 2 * m;
     const uint32_t blk = kind == PK_ROW ? (uint32_t)mb0 + r : 0u;
     const int64_t i = (int64_t)blk * kBlock + tid;
@@ -2415,19 +2816,23 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
     const dim3 rgrid(std::min<unsigned>(grid.x, 16384u));
     bool merged = false;
     if constexpr (DIM == 2) {
-      if (passes != 1 && A.drow && A.q2) {
-        // both pass-1 searches, the update and the pass-2 search in one
-        // sweep; the deferred rows after the pass-1 roots
+      if (passes != 1) {
         merged = true;
-        NS_LAUNCH("lim12", hipLaunchKernelGGL((k_lim2<DIM, 4, SEV, LT>), grid, block, 0, s,
-                                              G, A, gas));
-        NS_LAUNCH("root1", hipLaunchKernelGGL((k_root<DIM, 1, SEV, LT>), rgrid, block, 0, s,
-                                              G, A, gas));
-        NS_LAUNCH("lim2d", hipLaunchKernelGGL((k_lim2_rows<DIM, SEV, LT>), rgrid, block, 0, s,
-                                              G, A, gas));
-        NS_LAUNCH("root2", hipLaunchKernelGGL((k_root<DIM, 2, SEV, LT>), rgrid, block, 0, s,
-                                              G, A, gas));
-        NS_LAUNCH("fin", hipLaunchKernelGGL((k_fin<DIM, LT>), grid, block, 0, s, G, A, gas));
+        const dim3 wide(kWide), rows(spec_groups(G.nsrow) + lim_groups(G.N));
+        if (A.keep) {
+          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, true, LT>), lgrid,
+                                                    block, 0, s, G, A, gas));
+          NS_LAUNCH("lim_done", hipLaunchKernelGGL(k_lim_done<LT>, grid, block, 0, s, G, A));
+          NS_LAUNCH("lim_rows", hipLaunchKernelGGL((k_lim_rows<SEV, true, LT>), rows, wide, 0,
+                                                   s, G, A, gas));
+        } else {
+          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, false, LT>), lgrid,
+                                                    block, 0, s, G, A, gas));
+          NS_LAUNCH("lim_done", hipLaunchKernelGGL(k_lim_done<LT>, grid, block, 0, s, G, A));
+          NS_LAUNCH("lim_rows", hipLaunchKernelGGL((k_lim_rows<SEV, false, LT>), rows, wide, 0,
+                                                   s, G, A, gas));
+        }
+        NS_LAUNCH("fin", hipLaunchKernelGGL(k_fin_rows<LT>, rows, wide, 0, s, G, A));
       }
     }
     if (!merged) {
@@ -2438,10 +2843,7 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
       NS_LAUNCH("lim2", hipLaunchKernelGGL((k_lim2<DIM, 1, SEV, LT>), grid, block, 0, s, G,
                                            A, gas));
     } else {
-      if constexpr (DIM == 2) {
-        NS_LAUNCH("lim2", hipLaunchKernelGGL((k_lim2<DIM, 0, SEV, LT>), grid, block, 0, s,
-                                             G, A, gas));
-      } else {
+      if constexpr (DIM == 3) {
         NS_LAUNCH("lim2", hipLaunchKernelGGL((k_lim2_w4<DIM, 3, SEV, LT>), grid, block, 0, s,
                                              G, A, gas));
         NS_LAUNCH("lim2b", hipLaunchKernelGGL((k_lim2b<DIM, SEV, LT>), grid, block, 0, s,

@@ -7,8 +7,8 @@
 // within a slice: slot k of row i at ((i/64) W + k) 64 + i%64), so lane i of
 // a wavefront reading slot k of its row produces one coalesced access.  One
 // lane owns one row; the viscosity and low-order sweeps read the neighbours
-// along stencil lines (line_sweep.hpp), the limiter sweeps gather them through
-// the L1/L2 caches.  Sweeps, in dependency order (each needs the
+// along stencil lines (line_sweep.hpp), as the 2D limiter does; the other
+// limiter sweeps gather them through the L1/L2 caches.  Sweeps, in dependency order (each needs the
 // previous one complete over the whole mesh):
 //   k_prim   per node: sound speed a, a p^(-(g-1)/(2g)), eta, Phi
 //   k_visc   d^L_ij for j > i (Sec. 3.1), written to (i,j) and (j,i);
@@ -16,6 +16,8 @@
 //   k_dt     (auto time step only) per-block min of m_i / (2 sum_j d_ij)
 //   k_lo     d_ii, stage CFL check, U^L (eq. loworder), local bounds from
 //            the bar states (eq. bar_state), F^H_i (Sec. 3.2)
+//   (2D with two passes: k_lim_first, k_lim_done, k_lim_rows, k_fin_rows in
+//   place of the limiter sweeps below, which 3D and one pass keep)
 //   k_lim1   P_ij (Sec. 3.3) and the pass-1 line search l~_ij; entries
 //            whose entropy bound cuts inside (0, l_rho) go to a work list
 //   k_root   roots of the entropy bound for the listed entries, one lane
@@ -98,15 +100,20 @@ struct StageArgsT {
   // qcnt[p] counts the entries of pass p+1 (reset by k_lo).
   uint32_t *q;
   uint32_t *qcnt;
-  // 2D two-pass limiting in one sweep (k_lim2 MODE 4): the pass-2 work list
-  // q2 (W*Np entries; null: q, filled after q is emptied) and the deferred
-  // rows drow (Np entries, qcnt[2] of them; null: not used, qcnt has two
-  // counters)
+  // the pass-2 work list q2 (W*Np entries; null: q, filled after q is emptied)
   uint32_t *q2 = nullptr;
-  uint32_t *drow = nullptr;
   // 2D: per row, bit k set where the stored pass-2 product of slot k may be
-  // nonzero (written by the pass-2 search, read by k_fin); N entries
+  // nonzero; N entries
   uint32_t *nzm = nullptr;
+  // 2D: per row, bit k set where the row's own pass-1 search of slot k does
+  // not return 1 (k_lim_first); N entries
+  uint32_t *lim = nullptr;
+  // 2D: per slice of 64 rows, a bit for each interior row with a pair that
+  // is limited (k_lim_done); Np / 64 entries
+  uint64_t *todo = nullptr;
+  // 2D: keep l~, l~' of all entries and U^(1) of all rows (the last stage of
+  // a step, and ns_fe_stage); otherwise only what the stage itself reads
+  int keep = 1;
   // A pack of several meshes stepped together: member of every 256-row
   // workgroup (each member's rows start at a workgroup boundary; padding
   // rows are isolated nodes), member count and workgroup offsets of the

@@ -93,6 +93,13 @@ __device__ __forceinline__ void line_keep(T &...v) {
 
 // A wave-uniform global address as such: the offset of the lane is then added
 // by the load itself (scalar base, 32-bit lane offset).
+__device__ __forceinline__ uint32_t from_left(uint32_t end, uint32_t x) {
+  return __builtin_amdgcn_update_dpp((int)end, (int)x, 0x138, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint32_t from_right(uint32_t end, uint32_t x) {
+  return __builtin_amdgcn_update_dpp((int)end, (int)x, 0x130, 0xf, 0xf, false);
+}
+
 template <typename T>
 using vec2 = T __attribute__((ext_vector_type(2)));
 template <typename T>

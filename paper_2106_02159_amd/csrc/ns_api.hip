@@ -170,6 +170,8 @@ struct ns_solver {
   int *flags = nullptr;
   uint32_t *q = nullptr, *qcnt = nullptr;
   uint32_t *nzm = nullptr;  // 2D: slots with a pass-2 weight, per row
+  uint32_t *lim = nullptr;  // 2D: slots limited by the row's own search
+  uint64_t *todo = nullptr;  // 2D: rows with a limited pair, a bit each
   // host copies of device scalars (pageable: no pinned allocation, whose
   // release would synchronize the whole device)
   int hflags[4] = {0, 0, 0, 0};
@@ -187,6 +189,7 @@ struct ns_solver {
   double htau[1] = {0.0};
   int last_out = 1;        // buffer holding the last stage output
   bool stage_ran = false;  // a stage has run: its limiter arrays hold data
+  int keep = 1;            // the stage being launched keeps them
   // persistent steps (ns_step_cfl_persistent): per member (nmem + 1
   // entries) the first row block, work-list slice, slip slice and slip
   // entry; list counters, completion counters, ticket, stop words; the
@@ -230,8 +233,10 @@ struct ns_solver {
     b.U = a.U; b.Un = a.Un; b.out = a.out; b.aux = a.aux; b.UL = a.UL; b.bnds = a.bnds;
     b.U1 = a.U1; b.partial = a.partial; b.tau = a.tau; b.flags = a.flags;
     b.sa = a.sa; b.sb = a.sb; b.check_cfl = a.check_cfl; b.q = a.q; b.qcnt = a.qcnt;
-    b.q2 = a.q2; b.drow = a.drow; b.nzm = a.nzm;
+    b.q2 = a.q2; b.nzm = a.nzm; b.lim = a.lim;
+    b.todo = a.todo;
     b.seg = a.seg; b.mblk = a.mblk; b.nmem = a.nmem; b.check_low = a.check_low;
+    b.keep = a.keep;
     b.alpha = alphaf; b.d = df; b.FH = FHf; b.lt1 = lt1f; b.lt2 = lt2f;
     b.fp32_eval = fp32_eval && !redo_fp64;
     return b;
@@ -244,10 +249,12 @@ struct ns_solver {
     a.flags = flags; a.sa = sa; a.sb = sb; a.check_cfl = adaptive ? 0 : check;
     a.check_low = adaptive || fp32_eval ? 1 : 0;
     a.q = q; a.qcnt = qcnt;
-    a.q2 = q + (int64_t)W * Np;  // the pass-2 list and the deferred rows
-    a.drow = q + 2 * (int64_t)W * Np;
+    a.q2 = q + (int64_t)W * Np;  // the pass-2 list
     a.nzm = nzm;
+    a.lim = lim;
+    a.todo = todo;
     a.seg = seg; a.mblk = mblk; a.nmem = nmem;
+    a.keep = keep;
     return a;
   }
   int fail(int code, const std::string &msg) { err = msg; return code; }
@@ -416,9 +423,12 @@ int read_flags(ns_solver *s) {
   return NS_OK;
 }
 
+// keep: the limiter's arrays of this stage may be read later (ns_stats,
+// ns_get_debug): the last stage of a step
 void run_stage(ns_solver *s, int in, int out, double sa, double sb, int check,
-               bool auto_dt) {
+               bool auto_dt, bool keep) {
   s->stage_ran = true;
+  s->keep = keep ? 1 : 0;
   if (s->mixed)
     ns::launch_stage(s->dim, s->gas, s->devgraph32(), s->args32(in, out, sa, sb, check),
                      s->prm.indicator, s->prm.limiter, s->prm.passes, auto_dt,
@@ -456,13 +466,13 @@ int ssprk3_enqueue(ns_solver *s, double dt, bool auto_dt) {
   const int o1 = others(s->cur, 0), o2 = others(s->cur, 1);
   if (!auto_dt) ns::launch_set_scalar(s->tau, dt, s->stream);
   // w1 = E(u^n)
-  run_stage(s, s->cur, o1, 0.0, 1.0, auto_dt ? 0 : 1, auto_dt);
+  run_stage(s, s->cur, o1, 0.0, 1.0, auto_dt ? 0 : 1, auto_dt, false);
   run_slip(s, o1);
   // w2 = 3/4 u^n + 1/4 E(w1)
-  run_stage(s, o1, o2, 0.75, 0.25, 1, false);
+  run_stage(s, o1, o2, 0.75, 0.25, 1, false, false);
   run_slip(s, o2);
   // u^{n+1} = 1/3 u^n + 2/3 E(w2)
-  run_stage(s, o2, o1, 1.0 / 3.0, 2.0 / 3.0, 1, false);
+  run_stage(s, o2, o1, 1.0 / 3.0, 2.0 / 3.0, 1, false, true);
   run_slip(s, o1);
   s->last_out = o1;
   return o1;
@@ -828,9 +838,9 @@ int64_t footprint(const Layout &Lt, const ns_params *p) {
   b += 3 * nc * N * 8 + 4 * N * 8;                   // states, aux
   b += N * L + W * Np * L + nc * N * 8 + (nc + (dim == 3)) * N * L;  // alpha, d, U^L, F^H
   b += 3 * N * 8 + 2 * W * Np * L + nc * N * 8;      // bounds, l~ (2), U^(1)
-  b += N * 4;                                        // pass-2 weight mask
+  b += 2 * N * 4 + Np / 8;                           // pass-2 weight and pass-1 masks, rows
   b += nblocks * 8 + nm * (8 + 4 * 4 + 8);           // partial, tau, flags, time
-  b += (2 * W * Np + Np) * 4 + 4 * 4;                // root work lists, deferred rows
+  b += 2 * W * Np * 4 + 4 * 4;                       // root work lists
   b += nslip * 4 + dim * nslip * 8;                  // slip list
   if (Lt.pack) b += nblocks * 4 + (nm + 1) * 4;      // member of each workgroup
   b += 4 * (nm + 1) * 4 + 3 * nm * 4 + 4 + 4 * 4;    // persistent-step tables
@@ -967,6 +977,8 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
   NS_ALLOC(s->bnds, 3 * N);
   NS_ALLOC(s->U1, nc * N);
   NS_ALLOC(s->nzm, N);
+  NS_ALLOC(s->lim, N);
+  NS_ALLOC(s->todo, Np / 64);
   NS_ALLOC(s->partial, nblocks);
   NS_ALLOC(s->tau, s->nmem);
   NS_ALLOC(s->flags, 4 * s->nmem);
@@ -976,7 +988,7 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
     NS_ALLOC(s->mblk, s->nmem + 1);
   }
   // limiter root work list, large enough for every edge
-  NS_ALLOC(s->q, 2 * W * Np + Np);  // pass-1 and pass-2 lists, deferred rows
+  NS_ALLOC(s->q, 2 * W * Np);  // pass-1 and pass-2 lists
   NS_ALLOC(s->qcnt, 4);
   NS_ALLOC(s->pmblk, s->nmem + 1);
   NS_ALLOC(s->prblk, s->nmem + 1);
@@ -1939,7 +1951,7 @@ int ns_fe_stage(ns_solver *s, double dt) {
   const int o1 = others(s->cur, 0);
   ns::launch_clear_flags(s->flags, s->stream);
   ns::launch_set_scalar(s->tau, dt, s->stream);
-  run_stage(s, s->cur, o1, 0.0, 1.0, 1, false);
+  run_stage(s, s->cur, o1, 0.0, 1.0, 1, false, true);
   s->last_out = o1;
   int rc = read_flags(s);
   if (rc != NS_OK) return rc;
