@@ -1207,6 +1207,7 @@ __device__ __forceinline__ void lo_lines(const DevGraphT<LT> &G, const StageArgs
 template <int DIM, typename LT>
 __global__ __launch_bounds__(kBlock) void k_lo(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
   clear_lists(A, row_id() == 0);
+  if (DIM == 3 && blockIdx.x == 0 && threadIdx.x < 2 * 64) A.q2[8 * threadIdx.x] = 0;
   const uint32_t ns = spec_blocks<DIM>(G);
   if (blockIdx.x < ns) {
     lo_spec<DIM>(G, A, g);
@@ -1412,12 +1413,12 @@ __global__ __launch_bounds__(kBlock) void k_lim1(DevGraphT<LT> G, StageArgsT<LT>
 
 // MODE 0: convex, pass-1 update + pass-2 line search (2D, the persistent
 // steps); 1: convex with one pass, final; 2: l = 1 (unlimited high order),
-// final; 3: convex, pass-1 update only (3D: the pass-2 search is k_lim2b,
-// since both in one kernel need more registers than a SIMD lane has).
+// final; 3: convex, pass-1 update only (3D, the persistent steps: lim2b_row
+// follows, since both at once need more registers than a SIMD lane has).
 template <int DIM, int MODE, int SEV, typename LT>
 __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                          const Gas &g, uint32_t blk, int64_t i) {
-  // no fused multiply-adds of the compiler's choosing: MODE 0 must give the
+  // no fused multiply-adds of the compiler's choosing: MODE 0 and 3 must give the
   // bits of the launch path's kernels
 #pragma clang fp contract(off)
   using C = Cfg<DIM, NS_CH_LIM2>;
@@ -1432,6 +1433,14 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
   const double lam = 1.0 / G.lfac[i];
   double u1[NC];
   load_state<NC>(A.UL, N, i, u1);
+  // MODE 3 sums as the launch path does: all of P, less (1 - l) P of the
+  // limited pairs; rows that are not interior line by line
+  const bool in = MODE == 3 && colk.interior();
+  double sub[MODE == 3 ? NC : 1], part[MODE == 3 ? NC : 1], all[MODE == 3 ? NC : 1];
+  if constexpr (MODE == 3) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) sub[q] = part[q] = all[q] = 0.0;
+  }
   // 2D: the row's P_ij and l_ij stay for the pass-2 search: the P of the
   // first NS_LIM2_LDS off-diagonal slots in the lane's own LDS words (no
   // sharing between lanes, so no barrier), the rest in registers
@@ -1468,8 +1477,19 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
       double P[NC];
       make_P<DIM>(R, x[kk], P);
       const double l = MODE != 2 ? fmin(la[kk], lb[kk]) : 1.0;
+      if constexpr (MODE == 3) {
+        const double ls = lam * (1.0 - l);
 #pragma unroll
-      for (int q = 0; q < NC; ++q) u1[q] += lam * l * P[q];
+        for (int q = 0; q < NC; ++q) {
+          const double t = lam * P[q];
+          if (in) u1[q] += t;
+          else part[q] += t;
+          sub[q] += ls * P[q];
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) u1[q] += lam * l * P[q];
+      }
       if constexpr (CACHE) {
         const int o = k < C::W / 2 ? k : k - 1;  // off-diagonal ordinal
         if (o < NLDS) {
@@ -1482,8 +1502,19 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
         lc[k] = l;
       }
     }
+    if constexpr (MODE == 3) {
+      if ((ch + 1) * C::CH % 3 == 0) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          all[q] += part[q];
+          part[q] = 0.0;
+        }
+      }
+    }
   }
   if constexpr (MODE == 3) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) u1[q] = (in ? u1[q] : u1[q] + all[q]) - sub[q];
     store_state<NC>(A.U1, N, i, u1);
   } else if constexpr (MODE == 1 || MODE == 2) {
     finish<DIM>(G, A, i, u1);
@@ -1492,7 +1523,7 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
     const Bounds b = load_bounds(A, N, i);
     LT *__restrict__ lt2 = A.lt2;
     uint32_t slow = 0;
-    uint32_t nzm = 0;  // slots whose stored product may be nonzero (k_fin)
+    uint32_t nzm = 0;  // slots whose stored product may be nonzero (fin_row)
     if constexpr (!CACHE) {
       // reload the neighbour data rather than keep a whole row of it live
       asm volatile("" ::: "memory");
@@ -1578,7 +1609,7 @@ __global__ __launch_bounds__(kBlock) void k_lim2(DevGraphT<LT> G, StageArgsT<LT>
 }
 
 // ---------------------------------------------------------------------------
-// 2D, two passes (launch path).  Away from shocks the whole of P_ij passes
+// Two passes (launch path).  First 2D.  Away from shocks the whole of P_ij passes
 // both searches of every pair of a row: l_ij = 1, nothing is left for pass 2,
 // and the row's result is U^L + lambda_i sum_j P_ij.  So
 //   k_lim_first   sweeps along stencil lines: forms every P_ij, tests whether
@@ -1619,6 +1650,23 @@ __device__ __forceinline__ bool limit_is_one(const Gas &g, const double *u, cons
   return entropy_ok<DIM, SEV>(g, u, P, 1.0, b.pmin, b.pmin5) && rho;
 }
 
+// F^H / m and alpha of a line (3D: alpha is F^H's sixth component).
+template <int DIM, typename LT>
+__device__ __forceinline__ void line_flux(const StageArgsT<LT> &A, int64_t N, int64_t b,
+                                          uint32_t off, double *f, double &al) {
+  constexpr int NC = DIM + 2;
+  if constexpr (DIM == 3) {
+    double f6[NC + 1];
+    line_state<NC + 1>(A.FH, N, b, off, f6);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) f[q] = f6[q];
+    al = f6[NC];
+  } else {
+    line_state<NC>(A.FH, N, b, off, f);
+    al = line_ld(A.alpha, b, off);
+  }
+}
+
 constexpr uint32_t kSpecRow = 0x80000000u;  // bit of A.lim: a listed row
 constexpr int kWide = 512;                  // lanes: 64 rows of 8 pairs
 
@@ -1638,8 +1686,7 @@ __device__ __forceinline__ void lim_first_lines(const DevGraphT<LT> &G, const St
   const Line own = make_line(r0, 0, N, tid);
   RowCtx<DIM> R;
   line_state<NC>(A.U, N, own.b, own.c, R.ui);
-  line_state<NC>(A.FH, N, own.b, own.c, R.fi);
-  R.ali = line_ld(A.alpha, own.b, own.c);
+  line_flux<DIM>(A, N, own.b, own.c, R.fi, R.ali);
   R.coef = A.tau[A.seg ? geo_ld(&A.seg[blk]) : 0] * line_ld(G.crm, own.b, own.c);
   double ul[NC], u1[NC];
   line_state<NC>(A.UL, N, own.b, own.c, ul);
@@ -1672,13 +1719,11 @@ __device__ __forceinline__ void lim_first_lines(const DevGraphT<LT> &G, const St
       ac = R.ali;
     } else {
       line_state<NC>(A.U, N, L.b, L.c, uc);
-      line_state<NC>(A.FH, N, L.b, L.c, fc);
-      ac = line_ld(A.alpha, L.b, L.c);
+      line_flux<DIM>(A, N, L.b, L.c, fc, ac);
     }
     if (edge) {
       line_state<NC>(A.U, N, L.b, L.h, uh);
-      line_state<NC>(A.FH, N, L.b, L.h, fh);
-      ah = line_ld(A.alpha, L.b, L.h);
+      line_flux<DIM>(A, N, L.b, L.h, fh, ah);
     }
     static_for<0, 3>([&](auto along) __attribute__((always_inline)) {
       constexpr int dx = decltype(along)::value - 1;
@@ -1730,19 +1775,24 @@ __device__ __forceinline__ void make_P_both(const RowCtx<DIM> &R, const PIn<DIM>
   }
 }
 
-// A listed row's mask: the own searches, one lane per line.
-template <int DIM, int SEV, typename LT>
+// A listed row's mask: the own searches, one lane per line; 3D: the sum too
+// (2D: k_lim_rows forms it).
+template <int DIM, int SEV, bool KEEP, typename LT>
 __device__ __forceinline__ void lim_first_spec(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                                const Gas &g) {
+#pragma clang fp contract(off)
   constexpr int NC = DIM + 2;
   const SpecLane<DIM> L(G);
   const int64_t N = G.N, i = L.i;
   const BoxNbr<DIM> jv = row_nbr<DIM>(G, i);
   RowCtx<DIM> R;
   load_row<DIM>(G, A, i, A.tau[member(A, i)], R);
-  double ul[NC];
+  double ul[NC], part[NC];
   load_state<NC>(A.UL, N, i, ul);
   const Bounds b = load_bounds(A, N, i);
+  const double lam = 1.0 / G.lfac[i];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) part[q] = 0.0;
   uint32_t mask = 0;
 #pragma unroll 1
   for (int t = 0; t < 3; ++t) {
@@ -1752,17 +1802,34 @@ __device__ __forceinline__ void lim_first_spec(const DevGraphT<LT> &G, const Sta
     gather_P<DIM>(G, A, eidx<DIM>(k, i), j >= 0 ? j : i, jv.mass(k), x);
     double P[NC];
     make_P<DIM>(R, x, P);
-    if (j >= 0 && j != i && !limit_is_one<DIM, SEV>(g, ul, P, b)) mask |= 1u << k;
+    if (j >= 0 && j != i) {
+      if (!limit_is_one<DIM, SEV>(g, ul, P, b)) mask |= 1u << k;
+      if constexpr (DIM == 3) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) part[q] += lam * P[q];
+        if (KEEP && L.ok) {
+          A.lt1[eidx<DIM>(k, i)] = LT(1);
+          A.lt2[eidx<DIM>(k, i)] = LT(0);
+        }
+      }
+    }
   }
 #pragma unroll
   for (int l = 1; l < SpecLane<DIM>::NL; ++l) mask |= __shfl(mask, min(L.base + l, 63));
-  if (L.ok && L.line == 0) A.lim[i] = mask | kSpecRow;
+  if constexpr (DIM == 3) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) part[q] = ul[q] + L.sum(part[q]);
+  }
+  if (L.ok && L.line == 0) {
+    A.lim[i] = mask | kSpecRow;
+    if constexpr (DIM == 3) store_state<NC>(A.U1, N, i, part);
+  }
 }
 
 template <int DIM, int SEV, bool KEEP, typename LT>
 __global__ __launch_bounds__(kBlock) void k_lim_first(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
   const uint32_t ns = spec_blocks<DIM>(G);
-  if (blockIdx.x < ns) lim_first_spec<DIM, SEV, LT>(G, A, g);
+  if (blockIdx.x < ns) lim_first_spec<DIM, SEV, KEEP, LT>(G, A, g);
   else lim_first_lines<DIM, SEV, KEEP, LT>(G, A, g, blockIdx.x - ns);
 }
 
@@ -1837,7 +1904,9 @@ __device__ __forceinline__ void lim_pairs(const DevGraphT<LT> &G, const StageArg
       }
       if (pend) {
         const double p2 = pm * pm;
-        const double r = entropy_root_fast<2, SEV>(g, us, Ps, nbr ? rj : r0, pm, p2 * p2 * pm);
+        // (the bracket as the sweeps store it)
+        const double lr = (double)to_lt_down<LT>(nbr ? rj : r0);
+        const double r = entropy_root_fast<2, SEV>(g, us, Ps, lr, pm, p2 * p2 * pm);
         if (nbr) rj = r;
         else r0 = r;
         pend &= pend - 1;
@@ -2062,17 +2131,377 @@ __global__ __launch_bounds__(kWide) void k_fin_rows(DevGraphT<LT> G, StageArgsT<
   }
 }
 
-// 3D: at most 4 waves per SIMD.  The 3D pass-1 update needs 82 VGPRs and
-// would run 5 waves, whose extra gathers evict neighbour rows from L2 before
-// their reuse (1.8x the HBM traffic, 4.6 instead of 4.1 ms per 256^3
-// launch).
-template <int DIM, int MODE, int SEV, typename LT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 4))) void k_lim2_w4(
-    DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
-  lim2_row<DIM, MODE, SEV, LT>(G, A, g, blockIdx.x, row_id());
+// ---------------------------------------------------------------------------
+// 3D, two passes (launch path): k_lim_first as in 2D, then the limited entries
+// only.  In a shock tube four rows of five have some limited pair, but only a
+// tenth of the entries: a wave takes a slice of 64 rows, collects their limited
+// entries and gives each a lane, as many whole rows at a time as have at most
+// 64 of them.  A lane forms its entry's P_ij and P_ji, runs both searches
+// (roots included), and the rows' lanes subtract what pass 1 takes from
+// U^L + lambda sum P; then the pass-2 search of the same entries follows, and
+// rows without a pass-2 part are finished.  k_fin_entries adds that part of
+// the others the same way.  Against three sweeps over all entries that
+// gathered slot by slot, two root kernels and a final sweep (FP64, limiter and
+// final update of a stage): 6.47 -> 3.67 ms at 192^3, 1.99 -> 1.02 ms at 128^3,
+// and 0.55 -> 0.26 ms at 101 x 67 x 83 with FP32 coefficients.  k_lim_first
+// (1.18 ms at 192^3) is bound by arithmetic and load latency at 3 waves per
+// SIMD (held to 4 it spills: 1.68 ms).  k_lim_entries (1.67 ms) spends 0.42 ms
+// in the root finder, the rest on each group's chain of gathers; so does
+// k_fin_entries (0.80 ms).  3 waves per SIMD, since at 4 the former spills
+// (1.75 ms).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Pass-2 line search on (1 - l_ij) P_ij from U^(1) (stored by k_lim2<3>).
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t c, uint32_t lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(c, d);
+    if ((int)lane >= d) c += o;
+  }
+  return c;
+}
+
+// Workgroups of the listed rows, 64 to a wave.
+__host__ __device__ __forceinline__ uint32_t spec_slices(int nsrow) {
+  return (uint32_t)(nsrow + kBlock - 1) / kBlock;
+}
+// Counters of entries with a root (KEEP): kRootCnt of each pass, 8 words apart
+// in A.q2, cleared by k_lo and summed by k_fin_entries (a single one would
+// serialise the workgroups).
+constexpr uint32_t kRootCnt = 64;
+
+// Neighbour and m_ij of entry k of an interior row, by offset.
+struct Entry3 {
+  int32_t j;
+  double m;
+};
+__device__ __forceinline__ Entry3 interior_entry(const BoxGeom *geo, int64_t i, int k) {
+  const int dx = k % 3 - 1, dy = (k / 3) % 3 - 1, dz = k / 9 - 1;
+  const int n0 = geo_ld(&geo->n[0]), n1 = geo_ld(&geo->n[1]);
+  Entry3 e;
+  e.j = (int32_t)i + dx + n0 * (dy + n1 * dz);
+  e.m = geo->im[(dx ? 1 : 0) | (dy ? 2 : 0) | (dz ? 4 : 0)];
+  return e;
+}
+
+// Slots of row i at which the neighbour's mask holds the pair (i, j): slot k
+// is the neighbour's slot 26 - k.
+__device__ __forceinline__ uint32_t line_bits(const BoxGeom *geo, const uint32_t *mask,
+                                              int64_t r0, int64_t N, uint32_t tid) {
+  const int64_t n0 = geo_ld(&geo->n[0]), n01 = n0 * geo_ld(&geo->n[1]);
+  const bool edge = ((tid + 1) & 63) < 2;
+  uint32_t bits = 0;
+  static_for<0, 9>([&](auto line) __attribute__((always_inline)) {
+    constexpr int ln = decltype(line)::value, dy = ln % 3 - 1, dz = ln / 3 - 1;
+    const Line L = make_line(r0, dy * n0 + dz * n01, N, tid);
+    const uint32_t mc = line_ld(mask, L.b, L.c);
+    uint32_t mh = 0;
+    if (edge) mh = line_ld(mask, L.b, L.h);
+    bits |= ((from_left(mh, mc) >> (26 - 3 * ln)) & 1u) << (3 * ln);
+    if constexpr (ln != 4) bits |= ((mc >> (25 - 3 * ln)) & 1u) << (3 * ln + 1);
+    bits |= ((from_right(mh, mc) >> (24 - 3 * ln)) & 1u) << (3 * ln + 2);
+  });
+  return bits;
+}
+template <typename LT>
+__device__ __forceinline__ uint32_t listed_bits(const DevGraphT<LT> &G, const uint32_t *mask,
+                                                int64_t i) {
+  const BoxNbr<3> nb = row_nbr<3>(G, i);
+  uint32_t bits = 0;
+#pragma unroll 1
+  for (int k = 0; k < 27; ++k) {
+    const int32_t j = nb[k];
+    if (k != 13 && j >= 0) bits |= ((mask[j] >> (26 - k)) & 1u) << k;
+  }
+  return bits;
+}
+
+template <int SEV, bool KEEP, typename LT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) void
+k_lim_entries(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
+#pragma clang fp contract(off)
+  constexpr int NC = 5, NW = kBlock / 64;
+  __shared__ double vals[NW][NC][64], nbw[NW][11][64];
+  __shared__ uint32_t nzs[NW][64];
+  __shared__ uint16_t ids[NW][64];
+  const int64_t N = G.N;
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t ns = spec_slices(G.nsrow);
+  const bool front = blockIdx.x < ns;
+  int64_t i;
+  bool act;
+  uint32_t lim = 0;
+  const BoxGeom *geo = G.geo;
+  if (front) {
+    const int t = (int)(blockIdx.x * kBlock + tid);
+    act = t < G.nsrow;
+    i = G.srow[min(t, G.nsrow - 1)];
+    lim = (A.lim[i] & 0x7ffffffu) | listed_bits(G, A.lim, i);
+  } else {
+    const uint32_t blk = blockIdx.x - ns;
+    const int64_t r0 = (int64_t)blk * kBlock;
+    geo = block_geo(G, blk);
+    act = line_row(G, r0 + tid);
+    i = min(r0 + (int64_t)tid, N - 1);
+    lim = (A.lim[i] & 0x7ffffffu) |
+          line_bits(geo, A.lim, r0, N, tid);
+  }
+  if (!act) lim = 0;
+  const int mem = member(A, i);
+  double u1[NC];
+  load_state<NC>(A.U1, N, i, u1);
+  nzs[wv][lane] = 0;
+  const uint32_t cnt = (uint32_t)__builtin_popcount(lim);
+  const uint32_t upto = wave_scan(cnt, lane);
+  uint32_t start = 0, base = 0, n1 = 0, n2 = 0;
+  while (start < 64) {
+    // rows start .. end-1: their entries fill at most the wave's lanes
+    const uint64_t fits = __ballot(lane >= start && upto - base <= 64);
+    const uint32_t end = start + (uint32_t)__builtin_popcountll(fits);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)end - 1) - base;
+    const bool mine = lane >= start && lane < end;
+    const uint32_t p0 = upto - cnt - base;  // this row's first entry
+    if (total) {
+      wave_sync();
+      if (mine) {
+        uint32_t m = lim;
+        for (uint32_t p = p0; m; ++p) {
+          ids[wv][p] = (uint16_t)(lane << 5 | (uint32_t)__builtin_ctz(m));
+          m &= m - 1;
+        }
+      }
+      wave_sync();
+      const bool ok = lane < total;
+      const uint32_t id = ids[wv][ok ? lane : 0];
+      const int r = (int)(id >> 5), k = (int)(id & 31u);
+      const int64_t ir = __shfl((int)i, r);
+      const double tau = A.tau[__shfl(mem, r)];
+      Entry3 en;
+      if (front) {
+        const BoxNbr<3> nb = row_nbr<3>(G, ir);
+        en.j = nb[k];
+        en.m = nb.mass(k);
+      } else {
+        en = interior_entry(geo, ir, k);
+      }
+      const int64_t e = eidx<3>(k, ir);
+      const double lam = 1.0 / G.lfac[ir];
+      double P[NC], own, rj = 1.0, ul[NC];
+      Bounds b;
+      uint32_t pend = 0;
+      {
+        RowCtx<3> R;
+        PIn<3> x;
+        double uj[NC], Pj[NC];
+        load_row<3>(G, A, ir, tau, R);
+        gather_P<3>(G, A, e, en.j, en.m, x);
+        load_state<NC>(A.UL, N, ir, ul);
+        load_state<NC>(A.UL, N, en.j, uj);
+        b = load_bounds(A, N, ir);
+        const Bounds bj = load_bounds(A, N, en.j);
+        make_P_both<3>(R, x, tau * G.crm[en.j], P, Pj);
+        if (ok && limit_fast<3, SEV>(g, uj, Pj, bj, &rj)) {
+          pend = 2;
+#pragma unroll
+          for (int q = 0; q < NC; ++q) {
+            nbw[wv][q][lane] = uj[q];
+            nbw[wv][NC + q][lane] = Pj[q];
+          }
+          nbw[wv][2 * NC][lane] = bj.pmin;
+        }
+      }
+      double s1 = 1.0, l2 = 0.0;
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+        double r0 = pass ? 0.0 : 1.0;
+        const bool slow = ok && s1 != 0.0 && limit_fast<3, SEV>(g, ul, P, b, &r0);
+        if (slow) pend |= 1;
+        if (KEEP) (pass ? n2 : n1) += (uint32_t)__builtin_popcountll(__ballot(slow));
+#pragma unroll 1
+        while (__any(pend)) {  // the root finder, for every lane's next search
+          const bool nbr = pend == 2;
+          double us[NC], Ps[NC], pm = b.pmin;
+#pragma unroll
+          for (int q = 0; q < NC; ++q) {
+            us[q] = ul[q];
+            Ps[q] = P[q];
+          }
+          if (nbr) {
+#pragma unroll
+            for (int q = 0; q < NC; ++q) {
+              us[q] = nbw[wv][q][lane];
+              Ps[q] = nbw[wv][NC + q][lane];
+            }
+            pm = nbw[wv][2 * NC][lane];
+          }
+          if (pend) {
+            const double p2 = pm * pm;
+            const double lr = (double)to_lt_down<LT>(nbr ? rj : r0);
+            const double x = entropy_root_fast<3, SEV>(g, us, Ps, lr, pm, p2 * p2 * pm);
+            if (nbr) rj = x;
+            else r0 = x;
+            pend &= pend - 1;
+          }
+        }
+        if (pass == 0) {
+          own = (double)to_lt_down<LT>(r0);
+          s1 = 1.0 - fmin(own, (double)to_lt_down<LT>(rj));
+          const double ls = lam * s1;
+#pragma unroll
+          for (int q = 0; q < NC; ++q) vals[wv][q][lane] = ls * P[q];
+          wave_sync();
+          if (mine) {  // in slot order
+            double sub[NC];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) sub[q] = 0.0;
+            for (uint32_t p = p0; p < p0 + cnt; ++p)
+#pragma unroll
+              for (int q = 0; q < NC; ++q) sub[q] += vals[wv][q][p];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) u1[q] -= sub[q];
+          }
+          wave_sync();
+          if (mine) {
+#pragma unroll
+            for (int q = 0; q < NC; ++q) vals[wv][q][lane] = u1[q];
+          }
+          wave_sync();
+#pragma unroll
+          for (int q = 0; q < NC; ++q) {
+            ul[q] = vals[wv][q][r];
+            P[q] *= s1;
+          }
+        } else {
+          l2 = r0 * s1;
+        }
+      }
+      const LT sv = to_lt_down<LT>(l2);
+      if (ok) {
+        if constexpr (KEEP) A.lt1[e] = (LT)own;
+        if (KEEP || sv != LT(0)) A.lt2[e] = sv;
+        if (sv != LT(0)) atomicOr(&nzs[wv][r], 1u << k);
+      }
+    }
+    start = end;
+    base += total;
+  }
+  wave_sync();
+  const uint32_t nz = nzs[wv][lane];
+  if (act) {
+    A.nzm[i] = nz;
+    if (KEEP || nz) store_state<NC>(A.U1, N, i, u1);
+    if (!nz) finish<3>(G, A, i, u1);
+  }
+  if constexpr (KEEP) {
+    if (lane == 0 && (n1 | n2)) {
+      uint32_t *c = A.q2 + 8 * (blockIdx.x % kRootCnt);
+      atomicAdd(c, n1);
+      atomicAdd(c + 8 * kRootCnt, n2);
+    }
+  }
+}
+
+// U = U^(1) + lambda_i sum l' (1 - l) P of the rows with a pass-2 part: their
+// entries' products by lanes as in k_lim_entries, added in slot order.
+template <typename LT>
+__global__ __launch_bounds__(kBlock) void k_fin_entries(DevGraphT<LT> G, StageArgsT<LT> A) {
+#pragma clang fp contract(off)
+  constexpr int NC = 5, NW = kBlock / 64;
+  __shared__ double vals[NW][NC][64];
+  __shared__ uint16_t ids[NW][64];
+  const int64_t N = G.N;
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t ns = spec_slices(G.nsrow);
+  const bool front = blockIdx.x < ns;
+  if (A.keep && blockIdx.x == 0 && tid < 2 * kRootCnt) {
+    uint32_t c = A.q2[8 * tid];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
+    if (lane == 0) A.qcnt[wv] = c;
+  }
+  int64_t i;
+  bool act;
+  uint32_t bits;  // (a product that its row did not store is 0: its bit is clear)
+  const BoxGeom *geo = G.geo;
+  if (front) {
+    const int t = (int)(blockIdx.x * kBlock + tid);
+    act = t < G.nsrow;
+    i = G.srow[min(t, G.nsrow - 1)];
+    bits = listed_bits(G, A.nzm, i);
+  } else {
+    const uint32_t blk = blockIdx.x - ns;
+    const int64_t r0 = (int64_t)blk * kBlock;
+    geo = block_geo(G, blk);
+    act = line_row(G, r0 + tid);
+    i = min(r0 + (int64_t)tid, N - 1);
+    bits = line_bits(geo, A.nzm, r0, N, tid);
+  }
+  const uint32_t own = act ? A.nzm[i] : 0u, nz = own & bits;
+  if (!__any(own)) return;
+  const int mem = member(A, i);
+  double u2[NC];
+  load_state<NC>(A.U1, N, i, u2);
+  const uint32_t cnt = (uint32_t)__builtin_popcount(nz);
+  const uint32_t upto = wave_scan(cnt, lane);
+  uint32_t start = 0, base = 0;
+  while (start < 64) {
+    const uint64_t fits = __ballot(lane >= start && upto - base <= 64);
+    const uint32_t end = start + (uint32_t)__builtin_popcountll(fits);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)upto, (int)end - 1) - base;
+    const bool mine = lane >= start && lane < end;
+    const uint32_t p0 = upto - cnt - base;
+    if (total) {
+      wave_sync();
+      if (mine) {
+        uint32_t m = nz;
+        for (uint32_t p = p0; m; ++p) {
+          ids[wv][p] = (uint16_t)(lane << 5 | (uint32_t)__builtin_ctz(m));
+          m &= m - 1;
+        }
+      }
+      wave_sync();
+      const bool ok = lane < total;
+      const uint32_t id = ids[wv][ok ? lane : 0];
+      const int r = (int)(id >> 5), k = (int)(id & 31u);
+      const int64_t ir = __shfl((int)i, r);
+      const double tau = A.tau[__shfl(mem, r)];
+      Entry3 en;
+      if (front) {
+        const BoxNbr<3> nb = row_nbr<3>(G, ir);
+        en.j = nb[k];
+        en.m = nb.mass(k);
+      } else {
+        en = interior_entry(geo, ir, k);
+      }
+      const int64_t e = eidx<3>(k, ir), et = eidx<3>(tslot<3>(k), en.j);
+      const double la = A.lt2[e], lb = A.lt2[et];
+      RowCtx<3> R;
+      PIn<3> x;
+      load_row<3>(G, A, ir, tau, R);
+      gather_P<3>(G, A, e, en.j, en.m, x);
+      const double w = 1.0 / G.lfac[ir] * fmin(la, lb);
+      double P[NC];
+      make_P<3>(R, x, P);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) vals[wv][q][lane] = w * P[q];
+      wave_sync();
+      if (mine)
+        for (uint32_t p = p0; p < p0 + cnt; ++p)
+#pragma unroll
+          for (int q = 0; q < NC; ++q) u2[q] += vals[wv][q][p];
+    }
+    start = end;
+    base += total;
+  }
+  if (own) finish<3>(G, A, i, u2);
+}
+
+// Pass-2 line search on (1 - l_ij) P_ij from U^(1) (stored by lim2_row).
 template <int DIM, int SEV, typename LT>
 __device__ __forceinline__ void lim2b_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                           const Gas &g, uint32_t blk, int64_t i) {
@@ -2110,7 +2539,7 @@ __device__ __forceinline__ void lim2b_row(const DevGraphT<LT> &G, const StageArg
       if (jc[kk] < 0 || jc[kk] == i) continue;
       double P[NC], l2 = 0.0;
       const double s1 = 1.0 - fmin(la[kk], lb[kk]);
-      // else the stored product is 0 (see k_lim2), and P_ij's inputs are
+      // else the stored product is 0, and P_ij's inputs are
       // not gathered
       if (s1 != 0.0) {
         PIn<DIM> x;
@@ -2133,11 +2562,6 @@ __device__ __forceinline__ void lim2b_row(const DevGraphT<LT> &G, const StageArg
       q2[t++] = (uint32_t)eidx<DIM>(k, i);
     }
   }
-}
-
-template <int DIM, int SEV, typename LT>
-__global__ __launch_bounds__(kBlock) void k_lim2b(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
-  lim2b_row<DIM, SEV, LT>(G, A, g, blockIdx.x, row_id());
 }
 
 // Row of a sliced-ELL edge index (inverse of eidx in the row).
@@ -2183,10 +2607,10 @@ __device__ __forceinline__ void root_range(const DevGraphT<LT> &G, const StageAr
   }
 }
 
-template <int DIM, int PASS, int SEV, typename LT>
+template <int DIM, int SEV, typename LT>
 __global__ __launch_bounds__(kBlock) void k_root(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
-  root_range<DIM, PASS, SEV, LT>(G, A, g, blockIdx.x * kBlock + threadIdx.x,
-                                 gridDim.x * kBlock);
+  root_range<DIM, 1, SEV, LT>(G, A, g, blockIdx.x * kBlock + threadIdx.x,
+                              gridDim.x * kBlock);
 }
 
 template <int DIM, typename LT>
@@ -2268,11 +2692,6 @@ __device__ __forceinline__ void fin_row(const DevGraphT<LT> &G, const StageArgsT
     }
   }
   finish<DIM>(G, A, i, u2);
-}
-
-template <int DIM, typename LT>
-__global__ __launch_bounds__(kBlock) void k_fin(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
-  fin_row<DIM, LT>(G, A, g, blockIdx.x, row_id());
 }
 
 template <int DIM, typename LT>
@@ -2815,6 +3234,24 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
     // blocks past its end exit at once
     const dim3 rgrid(std::min<unsigned>(grid.x, 16384u));
     bool merged = false;
+    if constexpr (DIM == 3) {
+      if (passes != 1) {
+        merged = true;
+        const dim3 egrid(spec_slices(G.nsrow) + grid.x);
+        if (A.keep) {
+          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, true, LT>), lgrid,
+                                                    block, 0, s, G, A, gas));
+          NS_LAUNCH("lim_entries", hipLaunchKernelGGL((k_lim_entries<SEV, true, LT>), egrid,
+                                                      block, 0, s, G, A, gas));
+        } else {
+          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, false, LT>), lgrid,
+                                                    block, 0, s, G, A, gas));
+          NS_LAUNCH("lim_entries", hipLaunchKernelGGL((k_lim_entries<SEV, false, LT>), egrid,
+                                                      block, 0, s, G, A, gas));
+        }
+        NS_LAUNCH("fin", hipLaunchKernelGGL(k_fin_entries<LT>, egrid, block, 0, s, G, A));
+      }
+    }
     if constexpr (DIM == 2) {
       if (passes != 1) {
         merged = true;
@@ -2835,24 +3272,13 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
         NS_LAUNCH("fin", hipLaunchKernelGGL(k_fin_rows<LT>, rows, wide, 0, s, G, A));
       }
     }
-    if (!merged) {
-    NS_LAUNCH("lim1", hipLaunchKernelGGL((k_lim1<DIM, SEV, LT>), grid, block, 0, s, G, A, gas));
-    NS_LAUNCH("root1", hipLaunchKernelGGL((k_root<DIM, 1, SEV, LT>), rgrid, block, 0, s, G,
-                                          A, gas));
-    if (passes == 1) {
+    if (!merged) {  // one pass
+      NS_LAUNCH("lim1", hipLaunchKernelGGL((k_lim1<DIM, SEV, LT>), grid, block, 0, s, G, A,
+                                           gas));
+      NS_LAUNCH("root1", hipLaunchKernelGGL((k_root<DIM, SEV, LT>), rgrid, block, 0, s, G,
+                                            A, gas));
       NS_LAUNCH("lim2", hipLaunchKernelGGL((k_lim2<DIM, 1, SEV, LT>), grid, block, 0, s, G,
                                            A, gas));
-    } else {
-      if constexpr (DIM == 3) {
-        NS_LAUNCH("lim2", hipLaunchKernelGGL((k_lim2_w4<DIM, 3, SEV, LT>), grid, block, 0, s,
-                                             G, A, gas));
-        NS_LAUNCH("lim2b", hipLaunchKernelGGL((k_lim2b<DIM, SEV, LT>), grid, block, 0, s,
-                                              G, A, gas));
-      }
-      NS_LAUNCH("root2", hipLaunchKernelGGL((k_root<DIM, 2, SEV, LT>), rgrid, block, 0, s, G,
-                                            A, gas));
-      NS_LAUNCH("fin", hipLaunchKernelGGL((k_fin<DIM, LT>), grid, block, 0, s, G, A, gas));
-    }
     }
   }
 #undef NS_LAUNCH

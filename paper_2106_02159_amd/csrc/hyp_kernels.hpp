@@ -16,17 +16,21 @@
 //   k_dt     (auto time step only) per-block min of m_i / (2 sum_j d_ij)
 //   k_lo     d_ii, stage CFL check, U^L (eq. loworder), local bounds from
 //            the bar states (eq. bar_state), F^H_i (Sec. 3.2)
-//   (2D with two passes: k_lim_first, k_lim_done, k_lim_rows, k_fin_rows in
-//   place of the limiter sweeps below, which 3D and one pass keep)
-//   k_lim1   P_ij (Sec. 3.3) and the pass-1 line search l~_ij; entries
-//            whose entropy bound cuts inside (0, l_rho) go to a work list
+//   two limiter passes:
+//   k_lim_first    P_ij (Sec. 3.3), U^L + lambda_i sum P and the mask of the
+//                  pairs whose pass-1 line search does not return 1
+//   2D: k_lim_done finishes the rows without such a pair, k_lim_rows runs both
+//                  passes (roots of the entropy bound included) for the others,
+//                  8 lanes each, k_fin_rows adds the pass-2 part
+//   3D: k_lim_entries runs both passes, a lane per limited entry, and finishes
+//                  the rows without a pass-2 part, k_fin_entries the others
+//   one pass:
+//   k_lim1   P_ij and the pass-1 line search l~_ij; entries whose entropy
+//            bound cuts inside (0, l_rho) go to a work list
 //   k_root   roots of the entropy bound for the listed entries, one lane
 //            per entry (the rare slow path, kept out of the row sweeps)
-//   k_lim2   l_ij = min(l~_ij, l~_ji), U^(1) = U^L + lambda_i sum l P;
-//            pass-2 line search on (1 - l) P, stored as l~'_ij (1 - l_ij)
-//            (or the final state for one pass)
-//   k_fin    l' (1-l) symmetrised, U = U^(1) + lambda_i sum l' (1-l) P, SSP
-//            combination a U^n + b U and admissibility flag
+//   k_lim2   l_ij = min(l~_ij, l~_ji), U = U^L + lambda_i sum l P
+//   each ends with the SSP combination a U^n + b U and the admissibility flag
 //   k_slip   slip post-processing at wall nodes (eq. slip_bc)
 #pragma once
 

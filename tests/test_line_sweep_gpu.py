@@ -57,3 +57,30 @@ def test_line_sweeps(n, per):
         out.append((t, s.get_state()))
     assert out[0][0] == out[1][0]
     assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("precision", [abi.PREC_FP64, abi.PREC_MIXED])
+@pytest.mark.parametrize("n", [(9, 9, 9), (66, 5, 5), (130, 4, 6), (34, 21, 4)],
+                         ids=lambda v: "x".join(map(str, v)))
+def test_limited_entries(n, precision):
+    """3D limiter by entries: interior slices with none, few and more than a
+    wavefront of limited entries (smooth on one side, rough on the other),
+    the same two steps as the general path row by row, bit for bit."""
+    mesh = W.Mesh(3, n, (0.0,) * 3, tuple(0.01 * k for k in n), (False,) * 3)
+    U = W.random_rough_state(mesh, seed=sum(n))
+    smooth = np.arange(mesh.N) % n[0] < n[0] // 2
+    U[:, smooth] = U[:, :1]
+    g = abi.Graph(mesh)
+    out = []
+    for persistent in (False, True):
+        print("limited entries", n, precision, persistent, flush=True)
+        s = abi.Solver(g, cfl=0.5, precision=precision)
+        s.set_state(U)
+        (s.step_cfl_persistent if persistent else s.step_cfl_async)(2)
+        while not s.query():
+            time.sleep(1e-3)
+        rc, t = s.async_finish()
+        assert rc == abi.NS_OK
+        out.append((t, s.get_state()))
+    assert out[0][0] == out[1][0]
+    assert np.array_equal(out[0][1], out[1][1])
