@@ -548,7 +548,9 @@ int run_cg(ns_solver *s, int ncomp, double cdt, const char *label, int *iters) {
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return s->hipfail(e, "parabolic CG");
     if (s->hcg->done || launched > s->vprm.cg_maxit) break;
-    batch = std::min(2 * batch, 16);
+    // (an iteration launched after convergence returns at once, but with
+    // multigrid that is some 30 launches, 60 us, to a readback's 20 us)
+    if (!mg) batch = std::min(2 * batch, 16);
   }
   *iters = s->hcg->it;
   const bool ok = s->hcg->bb == 0.0 || s->hcg->rr <= s->hcg->rtol2 * s->hcg->bb;
