@@ -5,4 +5,6 @@
 namespace ns {
 int current_device();         // hipGetDevice; 0 if it fails
 void use_device(int device);  // hipSetDevice
+void *make_stream();          // non-blocking, default priority; null if it fails
+void drop_stream(void *stream);
 }  // namespace ns

@@ -68,6 +68,7 @@ struct Unit {
   std::vector<Request *> mem;
   ns_solver *s = nullptr;
   ns_pack *k = nullptr;
+  void *stream = nullptr;  // the server's, given back when the unit ends
   int steps = 0, enqueued = 0;
   int64_t bytes = 0;
   std::future<int> ready;  // set-up in a worker thread, until collected
@@ -82,6 +83,9 @@ struct ns_server {
   int device = 0;  // the creating thread's device, for the set-up threads
   std::deque<Request *> queue;
   std::vector<Unit *> running;
+  // idle streams of ended units, at most max_running with those in use: a
+  // stream takes 1.9 ms to create.  Only the caller's thread touches the list.
+  std::vector<void *> streams;
   std::map<int64_t, std::unique_ptr<Request>> all;
   int64_t used = 0;
   int64_t next_id = 1;
@@ -101,6 +105,8 @@ void release(ns_server *sv, Unit *u) {
   if (u->k) ns_pack_destroy(u->k);
   u->s = nullptr;
   u->k = nullptr;
+  if (u->stream) sv->streams.push_back(u->stream);  // (its work has ended)
+  u->stream = nullptr;
   for (Request *r : u->mem) release_graph(r);
   sv->used -= u->bytes;
 }
@@ -143,15 +149,16 @@ int inflight(Unit *u, int *n) {
 // Worker thread: create the unit's solver or pack and set the states.
 int prepare(const ns_params prm, int device, Unit *u) {
   ns::use_device(device);
+  if (!u->stream) u->stream = ns::make_stream();  // (null: the solver's own)
   int rc;
   if (u->mem.size() == 1) {
     Request *r = u->mem[0];
-    rc = ns_solver_create(r->g, &prm, nullptr, &u->s);
+    rc = ns_solver_create(r->g, &prm, u->stream, &u->s);
     if (rc == NS_OK) rc = ns_set_state(u->s, r->u0.data(), 0);
   } else {
     std::vector<const ns_graph *> gs;
     for (Request *r : u->mem) gs.push_back(r->g);
-    rc = ns_pack_create(gs.data(), (int)gs.size(), &prm, nullptr, &u->k);
+    rc = ns_pack_create(gs.data(), (int)gs.size(), &prm, u->stream, &u->k);
     for (size_t m = 0; rc == NS_OK && m < u->mem.size(); ++m)
       rc = ns_pack_set_state(u->k, (int)m, u->mem[m]->u0.data());
   }
@@ -283,6 +290,7 @@ void ns_server_destroy(ns_server *sv) {
     delete u;
   }
   for (auto &kv : sv->all) release_graph(kv.second.get());
+  for (void *st : sv->streams) ns::drop_stream(st);
   delete sv;
 }
 
@@ -392,6 +400,10 @@ int ns_server_progress(ns_server *sv, int *n_finished) {
     for (Request *r : u->mem) {
       r->t_admit = t0;
       r->state = RUNNING;
+    }
+    if (!sv->streams.empty()) {
+      u->stream = sv->streams.back();
+      sv->streams.pop_back();
     }
     u->ready = std::async(std::launch::async, prepare, sv->prm.solver, sv->device, u);
     u->preparing = true;
