@@ -307,7 +307,8 @@ template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_prim(int64_t N,
                                                  const double *__restrict__ U,
                                                  double *__restrict__ aux,
-                                                 Gas g) {
+                                                 Gas g, int *clear) {
+  if (clear && blockIdx.x == 0 && threadIdx.x < 4) clear[threadIdx.x] = 0;
   prim_row<DIM>(N, U, aux, g, plain_id());
 }
 
@@ -3191,7 +3192,8 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
     __VA_ARGS__;                                              \
     after(prof);                                              \
   } while (0)
-  NS_LAUNCH("prim", hipLaunchKernelGGL(k_prim<DIM>, grid, block, 0, s, G.N, A.U, A.aux, gas));
+  NS_LAUNCH("prim", hipLaunchKernelGGL(k_prim<DIM>, grid, block, 0, s, G.N, A.U, A.aux, gas,
+                                       A.clear));
   bool f32 = false;
   if constexpr (SEV == 1 && sizeof(LT) == 4) {
     if (indicator == 0 && A.fp32_eval) {
@@ -3291,7 +3293,8 @@ void dt_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A, do
   const dim3 grid = grid_for(G.N), block(kBlock);
   const dim3 lgrid(grid.x + spec_blocks<DIM>(G));
   before(prof, "prim");
-  hipLaunchKernelGGL(k_prim<DIM>, grid, block, 0, s, G.N, A.U, A.aux, gas);
+  hipLaunchKernelGGL(k_prim<DIM>, grid, block, 0, s, G.N, A.U, A.aux, gas,
+                     (int *)nullptr);
   after(prof);
   before(prof, "visc_dt");
   hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), lgrid, block, 0, s, G, A.U, A.aux, A.d,

@@ -105,6 +105,7 @@ struct StageArgsT {
   uint32_t *q;
   uint32_t *qcnt;
   // the pass-2 work list q2 (W*Np entries; null: q, filled after q is emptied)
+  int *clear = nullptr;  // the status flags, where the stage starts by clearing them
   uint32_t *q2 = nullptr;
   // 2D: per row, bit k set where the stored pass-2 product of slot k may be
   // nonzero; N entries

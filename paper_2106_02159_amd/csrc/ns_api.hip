@@ -190,6 +190,8 @@ struct ns_solver {
   bool graphs_off = false;
   bool async_open = false;
   double htau[1] = {0.0};
+  struct { double tau; int flags[4]; } hstat = {};  // both, as read back
+  bool clear_flags = false;  // the next stage clears the flags first
   int last_out = 1;        // buffer holding the last stage output
   bool stage_ran = false;  // a stage has run: its limiter arrays hold data
   int keep = 1;            // the stage being launched keeps them
@@ -236,7 +238,7 @@ struct ns_solver {
     b.U = a.U; b.Un = a.Un; b.out = a.out; b.aux = a.aux; b.UL = a.UL; b.bnds = a.bnds;
     b.U1 = a.U1; b.partial = a.partial; b.tau = a.tau; b.flags = a.flags;
     b.sa = a.sa; b.sb = a.sb; b.check_cfl = a.check_cfl; b.q = a.q; b.qcnt = a.qcnt;
-    b.q2 = a.q2; b.nzm = a.nzm; b.lim = a.lim;
+    b.q2 = a.q2; b.nzm = a.nzm; b.lim = a.lim; b.clear = a.clear;
     b.todo = a.todo;
     b.seg = a.seg; b.mblk = a.mblk; b.nmem = a.nmem; b.check_low = a.check_low;
     b.keep = a.keep;
@@ -252,6 +254,7 @@ struct ns_solver {
     a.flags = flags; a.sa = sa; a.sb = sb; a.check_cfl = adaptive ? 0 : check;
     a.check_low = adaptive || fp32_eval ? 1 : 0;
     a.q = q; a.qcnt = qcnt;
+    a.clear = clear_flags ? flags : nullptr;
     a.q2 = q + (int64_t)W * Np;  // the pass-2 list
     a.nzm = nzm;
     a.lim = lim;
@@ -424,14 +427,19 @@ int others(int cur, int k) {  // k-th (0/1) buffer index different from cur
 }
 
 int read_flags(ns_solver *s) {
-  hipError_t e = hipMemcpyAsync(s->hflags, s->flags, 4 * sizeof(int),
+  // one copy: the flags follow tau (of a single mesh; a pack's first member's
+  // apart)
+  hipError_t e = hipMemcpyAsync(&s->hstat, s->tau,
+                                s->nmem == 1 ? sizeof(s->hstat) : sizeof(double),
                                 hipMemcpyDeviceToHost, s->stream);
-  if (e != hipSuccess) return s->hipfail(e, "flag readback");
-  e = hipMemcpyAsync(s->htau, s->tau, sizeof(double), hipMemcpyDeviceToHost,
-                     s->stream);
-  if (e != hipSuccess) return s->hipfail(e, "dt readback");
+  if (e == hipSuccess && s->nmem > 1)
+    e = hipMemcpyAsync(s->hstat.flags, s->flags, sizeof(s->hstat.flags), hipMemcpyDeviceToHost,
+                       s->stream);
+  if (e != hipSuccess) return s->hipfail(e, "flag and dt readback");
   e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) return s->hipfail(e, "stream synchronize");
+  s->htau[0] = s->hstat.tau;
+  std::copy(s->hstat.flags, s->hstat.flags + 4, s->hflags);
   e = hipGetLastError();
   if (e != hipSuccess) return s->hipfail(e, "kernel launch");
   return NS_OK;
@@ -455,6 +463,7 @@ void run_stage(ns_solver *s, int in, int out, double sa, double sb, int check,
                      s->adaptive ? s->cfl_now : s->prm.cfl, s->stream, &Profiler::before,
                      &Profiler::after,
                      &s->prof);
+  s->clear_flags = false;
 }
 
 // Boundary post-processing of a stage result (Sec. 4.3): the non-reflecting
@@ -494,7 +503,7 @@ int ssprk3_enqueue(ns_solver *s, double dt, bool auto_dt) {
 
 int ssprk3(ns_solver *s, double dt, bool auto_dt, double *dt_out) {
   if (!s->has_state) return s->fail(NS_ESTATE, "no state set");
-  ns::launch_clear_flags(s->flags, s->stream);
+  s->clear_flags = true;
   int o1 = ssprk3_enqueue(s, dt, auto_dt);
   int rc = read_flags(s);
   if (rc != NS_OK) return rc;
@@ -503,7 +512,7 @@ int ssprk3(ns_solver *s, double dt, bool auto_dt, double *dt_out) {
     // row: the step again from the unchanged S[cur], in FP64 arithmetic
     ++s->fp64_redo;
     s->redo_fp64 = true;
-    ns::launch_clear_flags(s->flags, s->stream);
+    s->clear_flags = true;
     o1 = ssprk3_enqueue(s, dt, auto_dt);
     s->redo_fp64 = false;
     rc = read_flags(s);
@@ -1018,8 +1027,8 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
   NS_ALLOC(s->lim, N);
   NS_ALLOC(s->todo, Np / 64);
   NS_ALLOC(s->partial, nblocks);
-  NS_ALLOC(s->tau, s->nmem);
-  NS_ALLOC(s->flags, 4 * s->nmem);
+  NS_ALLOC(s->tau, 3 * s->nmem);  // tau, then 4 flags, of every member
+  s->flags = (int *)(s->tau + s->nmem);
   NS_ALLOC(s->tacc, s->nmem);
   if (s->pack) {
     NS_ALLOC(s->seg, nblocks);
@@ -1306,7 +1315,7 @@ int ns_step_adaptive(ns_solver *s, double c_start, double *dt, double *c_used) {
   for (int k = 0; k < 24; ++k, c *= 0.5) {
     s->adaptive = true;
     s->cfl_now = c;
-    ns::launch_clear_flags(s->flags, s->stream);
+    s->clear_flags = true;
     const int o1 = ssprk3_enqueue(s, 0.0, true);
     s->adaptive = false;
     const int rc = read_flags(s);
