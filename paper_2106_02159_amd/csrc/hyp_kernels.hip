@@ -1628,7 +1628,7 @@ __global__ __launch_bounds__(kBlock) void k_lim2(DevGraphT<LT> G, StageArgsT<LT>
 // worked through its own slice had up to 8 rounds of 8 rows, 13 us each.
 // Against one sweep that gathered every neighbour slot by slot, kept P for
 // pass 2, and listed the entries with a root for two further kernels (FP64,
-// limiter and final update of a stage): 2.61 -> 1.79 ms at 4096^2, 0.27 ->
+// limiter and final update of a stage): 2.61 -> 1.48 ms at 4096^2, 0.27 ->
 // 0.13 ms at 1001 x 1003, 0.11 -> 0.06 ms at 256^2; there the appends to the
 // lists, serial at their counters (15 ns each), and one lane's row of 8
 // searches took the time.  k_lim_first is bound by the latency of its line
@@ -1987,7 +1987,13 @@ __global__ __launch_bounds__(kBlock) void k_lim_done(DevGraphT<LT> G, StageArgsT
 }
 
 // Workgroups of k_lim_rows beside those of the listed rows: two per CU (what
-// fits), or as many as keep each at 128 slices (b, b + n, b + 2n, ...).
+// fits), or as many as keep each at 128 slices: one of every n, at a place
+// that moves on by kSkew each time.  Without the skew, where n slices are a
+// whole number of mesh lines, a workgroup had the same columns of every line,
+// and the few with a front along y had all of it (4096^2, steps 4 to 23 from
+// four quadrants: 1.51 ms at 0.4 waves per SIMD on average, now 0.22 ms, and
+// k_fin_rows 0.35 -> 0.06 ms; FP64 step 14.06 -> 9.25 ms).
+constexpr uint32_t kSkew = 37;
 constexpr int kSlices = 128;
 __host__ __device__ __forceinline__ uint32_t lim_groups(int64_t N) {
   const int64_t sl = (N + 63) / 64, n = (sl + kSlices - 1) / kSlices;
@@ -1996,6 +2002,10 @@ __host__ __device__ __forceinline__ uint32_t lim_groups(int64_t N) {
 __host__ __device__ __forceinline__ uint32_t lim_slices(int64_t N) {
   const uint32_t n = lim_groups(N);
   return (uint32_t)(((N + 63) / 64 + n - 1) / n);
+}
+// Slice t of workgroup b.
+__device__ __forceinline__ uint32_t lim_slice(uint32_t b, uint32_t t, uint32_t n) {
+  return t * n + (b + kSkew * t) % n;
 }
 __host__ __device__ __forceinline__ uint32_t spec_groups(int nsrow) {
   return (uint32_t)(nsrow + 63) / 64;
@@ -2027,7 +2037,7 @@ __global__ __launch_bounds__(kWide) __attribute__((amdgpu_waves_per_eu(4, 4))) v
       uint32_t sum = 0;
 #pragma unroll
       for (uint32_t t0 = 0; t0 < kSlices; t0 += 64) {
-        const uint32_t t = t0 + lane, sl = b + t * stride;
+        const uint32_t t = t0 + lane, sl = lim_slice(b, t, stride);
         const uint64_t w = t < most && sl < slices ? A.todo[sl] : 0;
         uint32_t c = (uint32_t)__builtin_popcountll(w);
         const uint32_t own = c;
@@ -2052,7 +2062,7 @@ __global__ __launch_bounds__(kWide) __attribute__((amdgpu_waves_per_eu(4, 4))) v
       if ((w >> lane) & 1u) {
         const uint32_t at = first[t] + __builtin_amdgcn_mbcnt_hi(
                                 (uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0));
-        const uint32_t row = (b + t * stride) * 64 + lane;
+        const uint32_t row = lim_slice(b, t, stride) * 64 + lane;
         list[at] = row;
         A.q[b * (most * 64) + at] = row;
       }

@@ -100,23 +100,25 @@ struct StageArgsT {
   int fp32_eval = 0;
   // Work list of the edges (sliced ELL index) whose line search needs the
   // root of the entropy bound; W*Np entries, so that it holds every edge.
-  // Pass 1 fills it and k_root<1> drains it before pass 2 fills it again;
+  // Pass 1 fills it and its roots are drained before pass 2 fills it again;
   // qcnt[p] counts the entries of pass p+1 (reset by k_lo).
   uint32_t *q;
   uint32_t *qcnt;
-  // the pass-2 work list q2 (W*Np entries; null: q, filled after q is emptied)
-  int *clear = nullptr;  // the status flags, where the stage starts by clearing them
+  // the pass-2 work list q2 (W*Np entries; null: q, filled after q is emptied).
+  // Launched two-pass limiting lists no roots: 2D keeps the limited rows of
+  // its slices in q and their number in q2, 3D its spread root counters in q2
   uint32_t *q2 = nullptr;
-  // 2D: per row, bit k set where the stored pass-2 product of slot k may be
+  int *clear = nullptr;  // the status flags, where the stage starts by clearing them
+  // per row, bit k set where the stored pass-2 product of slot k may be
   // nonzero; N entries
   uint32_t *nzm = nullptr;
-  // 2D: per row, bit k set where the row's own pass-1 search of slot k does
+  // per row, bit k set where the row's own pass-1 search of slot k does
   // not return 1 (k_lim_first); N entries
   uint32_t *lim = nullptr;
   // 2D: per slice of 64 rows, a bit for each interior row with a pair that
   // is limited (k_lim_done); Np / 64 entries
   uint64_t *todo = nullptr;
-  // 2D: keep l~, l~' of all entries and U^(1) of all rows (the last stage of
+  // keep l~, l~' of all entries and U^(1) of all rows (the last stage of
   // a step, and ns_fe_stage); otherwise only what the stage itself reads
   int keep = 1;
   // A pack of several meshes stepped together: member of every 256-row
