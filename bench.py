@@ -66,21 +66,23 @@ def kernel_bytes(name: str, dim: int, mixed: bool = False) -> float:
     table = {
         "prim": nc * n8 + (na - dim - 1) * n8,  # U -> a, b, eta, Phi
         "visc": nc * n8 + 3 * n8 + 1 + eL + nL,  # U, a, b, eta (v, p from U)
-        "visc_dt": (dim + 3) * n8 + 1 + eL,
         "dt_partial": eL + n8,
         "lo": eL + nc * n8 + 1 * n8 + nL + 3 * n8  # U, Phi (v, p from U), alpha, ...
               + nc * n8 + nc * nL + 3 * n8,
+        # two limiter passes: d, the row's U, U^L, F^H, alpha, m_i, lambda_i,
+        # bounds in; U^(1) and the mask out, in the last of three stages l~
+        # and l~' too
+        "lim_first": eL + rows + nL + 2 * n8 + 3 * n8 + nc * n8 + 4 + 2 * eL / 3,
+        # the rows with nothing left for pass 2: U^(1), U^n, masks in, U out
+        # (2D; 3D: in lim_entries).  What the other rows move depends on the
+        # data: lim_rows and fin count as 0
+        "lim_done": 3 * nc * n8 + 8,
+        "lim_entries": 3 * nc * n8 + 8,
+        "lim_rows": 0.0,
+        "fin": 0.0,
+        # one pass
         "lim1": eL + rows + nL + 2 * n8 + 3 * n8 + eL,
-        "lim2": (2 * eL + rows + nL + 2 * n8 + 3 * n8 + nc * n8 + eL
-                 if dim == 2 else  # 3D: pass-1 update only
-                 2 * eL + rows + nL + 2 * n8 + nc * n8),
-        "lim2b": 2 * eL + rows + nL + 2 * n8 + 3 * n8 + eL,
-        # 2D: both pass-1 searches, the update and the pass-2 search in one
-        # sweep (d, the row's U, U^L, F^H, alpha, m_i, lambda_i, bounds in;
-        # l~, U^(1), l~' out); the deferred rows are a small fraction
-        "lim12": 3 * eL + rows + nL + 2 * n8 + 3 * n8 + nc * n8,
-        "lim2d": 0.0,
-        "fin": 2 * eL + nc * (3 * n8 + nL) + nL + 2 * n8 + nc * n8,
+        "lim2": 2 * eL + rows + nL + 2 * n8 + 2 * nc * n8,
         "combine": 2 * nc * n8 + nc * n8,
         "slip": 0.0,
         "dt_final": 0.0,
