@@ -128,19 +128,25 @@ __device__ __forceinline__ float lambda_max_f32(const Gas &g, float uL, float pL
 
 // x^(7/5) for x > 0: x z with z = x^(2/5) from two Newton steps for z^5 = x^2
 // on an FP32 start (relative error e -> 2 e^2: 1e-6, 2e-12, rounding), x
-// scaled by a power of 2^5 into the FP32 range first.  A quarter of pow's
-// instructions; within 3 ulp of it.
+// scaled by a power of 2^5 into the FP32 range first.  The last step's
+// residual is formed with the rounding errors of its products and its
+// correction enters the final product, so the result is within 0.54 ulp, as
+// close as pow.  0 and infinity as pow.  A quarter
+// of pow's instructions.
 __device__ __forceinline__ double pow_seven_fifths(double x) {
 #pragma clang fp contract(off)  // the same bits in every kernel
   const int k = (__builtin_amdgcn_frexp_exp(x) * 205) >> 10;  // about e / 5
   const double y = ldexp(x, -5 * k), y2 = y * y;
   double z = (double)__builtin_amdgcn_exp2f(0.4f * __builtin_amdgcn_logf((float)y));
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
+  {
     const double z2 = z * z, z4 = z2 * z2;
     z = fma(fma(-z4, z, y2), 0.2 * fast_rcp(z4), z);
   }
-  return ldexp(y * z, 7 * k);
+  const double z2 = z * z, z4 = z2 * z2;
+  const double z4e = fma(z2, z2, -z4) + 2.0 * z2 * fma(z, z, -z2);
+  const double rest = fma(-z4, z, y2) + (fma(y, y, -y2) - z4e * z);
+  const double r = ldexp(fma(y, z, y * (rest * (0.2 * fast_rcp(z4)))), 7 * k);
+  return x == 0.0 || x == INFINITY ? x : r;
 }
 
 // psi(l) = eps(u + l P) - phi_min rho(u + l P)^gamma and its derivative.
@@ -246,8 +252,8 @@ __device__ __forceinline__ double entropy_root(const Gas &g, const double *u,
   return a;
 }
 
-// Root of the entropy bound for gamma = 7/5, to about 1e-9, on the polynomial
-// form of the test: with rho(l) = rho + l P_rho and A(l) = rho(l) E(l) -
+// Root of the entropy bound for gamma = 7/5 (the last Newton step, of at most
+// 1e-9, is taken in full precision) on the polynomial form of the test: with rho(l) = rho + l P_rho and A(l) = rho(l) E(l) -
 // |m(l)|^2/2 = a0 + a1 l + a2 l^2 (rho(l) eps(l)) the bound holds where
 // q = phi_min^5 rho^12 / A^5 <= 1.  Newton on log q, whose slope changes
 // little over (0, b) (on A^5 - phi_min^5 rho^12, twelfth powers, one lane in
@@ -294,31 +300,29 @@ __device__ __forceinline__ double entropy_root_seven(const double *u,
 }
 
 // Root of the entropy bound to the accuracy of psi itself.  For gamma = 7/5
-// the polynomial root (whose own rounding can leave it ~1e-12 away) is
-// followed by one Newton step on psi: psi is concave, so the tangent root x1
-// lies at or beyond the root (within round-off of it from such a close
-// start).  A point a below x1 with psi(a) >= 0 is then within x1 - a of the
-// root; the rounding of psi blurs its sign change over a band whose width
-// grows as psi flattens, so the step back from x1 grows (2e-15, 1.6e-14,
-// 1.3e-13, 1e-12) until psi confirms a feasible point.  If none is confirmed
-// (x1 was not close), the bracketing search on psi runs.
+// one Newton step on psi from the root of log q: psi is concave, so the
+// tangent's root x lies at or beyond the root (within round-off of it from such a
+// close start), and a point a below x with psi(a) >= 0 is within x - a of the
+// root.  The rounding of psi blurs its sign change over a band of some
+// 2^-52 E / |psi'|: the step back starts at a quarter of that, 2e-15 at least,
+// and doubles until psi confirms a feasible point.  If none is confirmed (x was
+// not close), the bracketing search on psi runs.  Against 128-bit roots, in
+// units of that band or 1e-14, the larger: rms 0.2 - 0.5, at most 3 (steps
+// of 2e-15 times powers of 8: 0.3 - 0.9, at most 17).
 template <int DIM, int SEV>
 __device__ __forceinline__ double entropy_root_fast(const Gas &g, const double *u,
                                                    const double *P, double lr,
                                                    double pmin, double pmin5) {
 #pragma clang fp contract(off)  // the same bits in every kernel
   if constexpr (SEV) {
-    const double x = entropy_root_seven<DIM>(u, P, lr, pmin5);
-    double d;
+    double x = entropy_root_seven<DIM>(u, P, lr, pmin5), d;
     const double f = psi_eval<DIM, SEV>(g, u, P, x, pmin, &d);
-    if (d < 0.0) {
-      const double x1 = x - f / d;
-      if (x1 > 0.0 && x1 <= lr) {
-        double h = 2e-15;
-        for (int k = 0; k < 4; ++k, h *= 8.0) {
-          const double a = fmax(x1 - h, 0.0);
-          if (psi_eval<DIM, SEV>(g, u, P, a, pmin, nullptr) >= 0.0) return a;
-        }
+    x -= f / d;
+    if (d < 0.0 && x > 0.0 && x <= lr) {
+      double h = fmax(2e-15, 0x1p-54 * fabs(fma(x, P[DIM + 1], u[DIM + 1]) / d));
+      for (int k = 0; k < 5; ++k, h *= 2.0) {
+        const double a = fmax(x - h, 0.0);
+        if (psi_eval<DIM, SEV>(g, u, P, a, pmin, nullptr) >= 0.0) return a;
       }
     }
   }

@@ -1,0 +1,164 @@
+"""The device arithmetic of the limiter's entropy root (csrc/euler.hpp) built
+for the host, the hardware's seed instructions replaced by rounded ones,
+against 128-bit arithmetic."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2106_02159_amd import build as B
+
+RUNTIME = """
+#pragma once
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+#define __device__
+#define __host__
+#define __forceinline__ inline
+using std::fma; using std::fmax; using std::fmin; using std::fabs; using std::sqrt;
+using std::ldexp;
+static long pow_calls;
+static inline double counted(double a, double b) { ++pow_calls; return std::pow(a, b); }
+#define pow(a, b) counted(a, b)
+// a seed of 26 correct bits
+static inline double seed(double r) {
+  uint64_t b;
+  std::memcpy(&b, &r, 8);
+  b &= ~((1ull << 26) - 1);
+  std::memcpy(&r, &b, 8);
+  return r;
+}
+static inline int exponent(double x) { int e = 0; if (std::isfinite(x)) std::frexp(x, &e); return e; }
+#define __builtin_amdgcn_rcp(x) seed(1.0 / (x))
+#define __builtin_amdgcn_rsq(x) seed(1.0 / std::sqrt(x))
+#define __builtin_amdgcn_frexp_exp(x) exponent(x)
+#define __builtin_amdgcn_exp2f(x) std::exp2((float)(x))
+#define __builtin_amdgcn_logf(x) std::log2((float)(x))
+#define __builtin_amdgcn_rcpf(x) (1.0f / (float)(x))
+#define __builtin_amdgcn_sqrtf(x) std::sqrt((float)(x))
+"""
+
+PROGRAM = """
+#include "hip/hip_runtime.h"
+#include "euler.hpp"
+#include <quadmath.h>
+using namespace ns;
+typedef __float128 Q;
+template <int D>
+Q psi(Q gamma, const double *u, const double *P, Q l, double pm) {
+  const Q r = u[0] + l * P[0], E = u[D + 1] + l * P[D + 1];
+  Q m2 = 0;
+  for (int k = 0; k < D; ++k) { const Q m = u[1 + k] + l * P[1 + k]; m2 += m * m; }
+  return E - m2 / (2 * r) - pm * powq(r, gamma);
+}
+template <int D, int S>
+void roots(const Gas &g, int n, const double *u, const double *P, const double *lr,
+           const double *pm, double *out, double *err, double *slope) {
+  const Q gamma = S ? (Q)7 / 5 : (Q)g.gamma, h = 1e-9;
+  for (int i = 0; i < n; ++i, u += D + 2, P += D + 2) {
+    const double p2 = pm[i] * pm[i];
+    out[i] = entropy_root_fast<D, S>(g, u, P, lr[i], pm[i], p2 * p2 * pm[i]);
+    Q a = 0, b = lr[i];
+    for (int k = 0; k < 75; ++k) {
+      const Q m = (a + b) / 2;
+      if (psi<D>(gamma, u, P, m, pm[i]) >= 0) a = m;
+      else b = m;
+    }
+    err[i] = (double)(out[i] - a);
+    slope[i] = (double)((psi<D>(gamma, u, P, a + h, pm[i]) - psi<D>(gamma, u, P, a, pm[i])) / h);
+  }
+}
+extern "C" long run(int dim, int seven, double gamma, int n, const double *u, const double *P,
+                    const double *lr, const double *pm, double *out, double *err, double *slope) {
+  Gas g{};
+  g.gamma = gamma;
+  pow_calls = 0;
+  auto f = dim == 2 ? (seven ? roots<2, 1> : roots<2, 0>) : seven ? roots<3, 1> : roots<3, 0>;
+  f(g, n, u, P, lr, pm, out, err, slope);
+  return pow_calls;
+}
+extern "C" void power(int n, const double *x, double *y, double *err) {
+  for (int i = 0; i < n; ++i) {
+    y[i] = pow_seven_fifths(x[i]);
+    const Q z = powq((Q)x[i], (Q)7 / 5);
+    const double w = std::fabs((double)z);
+    err[i] = (double)((y[i] - z) / (std::nextafter(w, INFINITY) - w));
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def device(tmp_path_factory):
+    d = tmp_path_factory.mktemp("root")
+    (d / "hip").mkdir()
+    (d / "hip" / "hip_runtime.h").write_text(RUNTIME)
+    (d / "root.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-O2", "-std=gnu++17", "-ffp-contract=off", "-mfma", "-fPIC", "-shared",
+                    "-Wno-unknown-pragmas", "-I", str(d), "-I", os.path.join(B.CSRC),
+                    str(d / "root.cpp"), "-o", str(d / "root.so"), "-lquadmath"], check=True)
+    return C.CDLL(str(d / "root.so"))
+
+
+def ptr(a):
+    return a.ctypes.data_as(C.c_void_p)
+
+
+def test_power(device):
+    """x^(7/5) as close as pow (1 ulp at most, here within 0.75), and pow's
+    values at 0 and infinity."""
+    rng = np.random.default_rng(0)
+    x = np.exp(rng.uniform(-200.0, 200.0, 200000))
+    y, err = np.empty_like(x), np.empty_like(x)
+    device.power(len(x), ptr(x), ptr(y), ptr(err))
+    assert np.abs(err).max() <= 0.75
+    x = np.array([0.0, np.inf])
+    device.power(2, ptr(x), ptr(y), ptr(err))
+    assert y[0] == 0.0 and y[1] == np.inf
+
+
+def lines(rng, n, dim, gamma, smallest, thin):
+    """States u, directions P of size `smallest` to 1 of the state, ends lr
+    and bounds pm that are crossed between 0 and lr."""
+    rho = np.exp(rng.uniform(np.log(1e-4 if thin else 0.1), np.log(8.0), n))
+    p = np.exp(rng.uniform(np.log(1e-4 if thin else 0.05), np.log(10.0), n))
+    v = rng.uniform(-3.0, 3.0, (n, dim))
+    E = p / (gamma - 1.0) + 0.5 * rho * (v ** 2).sum(axis=1)
+    u = np.column_stack([rho, rho[:, None] * v, E])
+    size = np.column_stack([rho] + [np.sqrt(2.0 * rho * E)] * dim + [E])
+    P = np.exp(rng.uniform(np.log(smallest), 0.0, (n, 1))) * size * rng.uniform(-1, 1, u.shape)
+    lr = np.where(rng.random(n) < 0.7, 1.0, rng.uniform(0.05, 1.0, n))
+
+    def bound(l):
+        w = u + l[:, None] * P
+        e = w[:, -1] - 0.5 * (w[:, 1:-1] ** 2).sum(axis=1) / w[:, 0]
+        return e / np.abs(w[:, 0]) ** gamma, (w[:, 0] > 0) & (e > 0)
+
+    pm, ok = bound(lr * rng.uniform(0.001, 0.999, n))
+    p1, ok1 = bound(lr)
+    ok = ok & ok1 & (bound(0.0 * lr)[0] > pm * (1 + 1e-9)) & (p1 < pm * (1 - 1e-9))
+    return [np.ascontiguousarray(a[ok]) for a in (u, P, lr, pm)]
+
+
+GAMMAS = [(1.4, 1)]
+
+
+@pytest.mark.parametrize("smallest,thin", [(1e-4, False), (1e-2, True), (0.3, False)])
+@pytest.mark.parametrize("gamma,seven", GAMMAS)
+@pytest.mark.parametrize("dim", [2, 3])
+def test_root(device, dim, gamma, seven, smallest, thin):
+    u, P, lr, pm = lines(np.random.default_rng(dim), 8000, dim, gamma, smallest, thin)
+    n = len(lr)
+    assert n > 1000
+    out, err, slope = np.empty(n), np.empty(n), np.empty(n)
+    device.run(dim, seven, C.c_double(gamma), n, ptr(u), ptr(P), ptr(lr), ptr(pm), ptr(out),
+               ptr(err), ptr(slope))
+    assert np.all((out >= 0.0) & (out <= lr))
+    # psi is known to about 2 units of 2^-52 E (the roundings of E, the kinetic
+    # energy and phi rho^gamma); the Newton step ends within 2 units of its
+    # root, the step back doubles: at most 2 (2 + 2)
+    unit = np.maximum(1e-14, 2.0 ** -52 * np.abs(u[:, -1] + out * P[:, -1]) / np.abs(slope))
+    assert np.abs(err / unit).max() <= 8.0
