@@ -150,10 +150,12 @@ __device__ __forceinline__ double pow_seven_fifths(double x) {
 }
 
 // psi(l) = eps(u + l P) - phi_min rho(u + l P)^gamma and its derivative.
-template <int DIM, int SEV>
-__device__ __forceinline__ double psi_eval(const Gas &g, const double *u,
+// power(rho, l) is rho^gamma.
+template <int DIM, class Power>
+__device__ __forceinline__ double psi_with(const Gas &g, const double *u,
                                            const double *P, double l,
-                                           double phi_min, double *dpsi) {
+                                           double phi_min, double *dpsi,
+                                           const Power &power) {
 #pragma clang fp contract(off)  // the same bits in every kernel
   const double r = fma(l, P[0], u[0]);
   double m2 = 0.0, mp = 0.0;
@@ -166,7 +168,7 @@ __device__ __forceinline__ double psi_eval(const Gas &g, const double *u,
   const double E = fma(l, P[DIM + 1], u[DIM + 1]);
   const double ir = 1.0 / r;
   const double eps = fma(-0.5 * m2, ir, E);
-  const double rg = SEV ? pow_seven_fifths(r) : pow(r, g.gamma);
+  const double rg = power(r, l);
   if (dpsi) {
     // d eps/dl = P_E - (m.P_m)/rho + |m|^2 P_rho / (2 rho^2)
     const double deps = fma(0.5 * m2 * ir * ir, P[0], fma(-mp, ir, P[DIM + 1]));
@@ -174,11 +176,22 @@ __device__ __forceinline__ double psi_eval(const Gas &g, const double *u,
   }
   return fma(-phi_min, rg, eps);
 }
+template <int DIM, int SEV>
+__device__ __forceinline__ double psi_eval(const Gas &g, const double *u,
+                                           const double *P, double l,
+                                           double phi_min, double *dpsi) {
+  return psi_with<DIM>(g, u, P, l, phi_min, dpsi, [&](double r, double) {
+    return SEV ? pow_seven_fifths(r) : pow(r, g.gamma);
+  });
+}
 
 // Is u + l P inside the entropy bound Phi >= phi_min?  For gamma = 7/5 the
 // test eps >= phi_min rho^(7/5) is taken division- and pow-free as
 // (rho eps)^5 >= phi_min^5 rho^12 with rho eps = rho E - |m|^2/2 (both sides
-// are non-negative exactly when eps >= 0); pmin5 = phi_min^5.
+// are non-negative exactly when eps >= 0); pmin5 = phi_min^5.  A general gamma
+// asks log q = log phi_min + (gamma + 1) log rho - log(rho eps) <= 0 in FP32
+// first, whose error is below 1e-6 of its terms' sizes, and pow only where that
+// leaves it open.
 template <int DIM, int SEV>
 __device__ __forceinline__ bool entropy_ok(const Gas &g, const double *u,
                                            const double *P, double l,
@@ -202,6 +215,12 @@ __device__ __forceinline__ bool entropy_ok(const Gas &g, const double *u,
     return A2 * A2 * A >= pmin5 * (r8 * r4);
   }
   else {
+    const float g1 = (float)(g.gamma + 1.0), lp = __builtin_amdgcn_logf((float)phi_min);
+    const float lr = g1 * __builtin_amdgcn_logf((float)r);
+    const float la = __builtin_amdgcn_logf((float)(r * E - 0.5 * m2));
+    const float lq = lp + lr - la, size = fabsf(lp) + fabsf(lr) + fabsf(la) + g1 + 2.0f;
+    // (false also for infinities and NaN: arguments beyond FP32, bounds <= 0)
+    if (fabsf(lq) > 1e-6f * size && size < 1e4f) return lq < 0.0f;
     return E - 0.5 * m2 / r - phi_min * pow(r, g.gamma) >= 0.0;
   }
 }
@@ -299,31 +318,96 @@ __device__ __forceinline__ double entropy_root_seven(const double *u,
   return x;
 }
 
-// Root of the entropy bound to the accuracy of psi itself.  For gamma = 7/5
-// one Newton step on psi from the root of log q: psi is concave, so the
-// tangent's root x lies at or beyond the root (within round-off of it from such a
-// close start), and a point a below x with psi(a) >= 0 is within x - a of the
-// root.  The rounding of psi blurs its sign change over a band of some
-// 2^-52 E / |psi'|: the step back starts at a quarter of that, 2e-15 at least,
-// and doubles until psi confirms a feasible point.  If none is confirmed (x was
-// not close), the bracketing search on psi runs.  Against 128-bit roots, in
-// units of that band or 1e-14, the larger: rms 0.2 - 0.5, at most 3 (steps
-// of 2e-15 times powers of 8: 0.3 - 0.9, at most 17).
+// The same for a general gamma, as a start for Newton steps on psi: log q =
+// log phi_min + (gamma + 1) log rho - log A in FP32 (to some 1e-6, in units of
+// the state's change along P), so no pow.  Returns the last iterate.
+template <int DIM>
+__device__ __forceinline__ double entropy_root_start(const Gas &g, const double *u,
+                                                     const double *P, double b, double pmin) {
+#pragma clang fp contract(off)  // the same bits in every kernel
+  double m0p = 0.0, pm2 = 0.0, m02 = 0.0;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) {
+    m0p = fma(u[1 + k], P[1 + k], m0p);
+    pm2 = fma(P[1 + k], P[1 + k], pm2);
+    m02 = fma(u[1 + k], u[1 + k], m02);
+  }
+  const double r0 = u[0], pr = P[0], E0 = u[DIM + 1], pE = P[DIM + 1];
+  const double a0 = fma(r0, E0, -0.5 * m02);
+  const double a1 = fma(r0, pE, fma(pr, E0, -m0p));
+  const double a2 = fma(pr, pE, -0.5 * pm2);
+  const float g1 = (float)(g.gamma + 1.0), lp = __builtin_amdgcn_logf((float)pmin);
+  double lo = 0.0, hi = b, x = 0.0;
+  for (int it = 0; it < 20; ++it) {
+    const double r = fma(x, pr, r0);
+    const double A = fma(x, fma(x, a2, a1), a0);
+    const float lq = lp + g1 * __builtin_amdgcn_logf((float)r) - __builtin_amdgcn_logf((float)A);
+    if (A > 0.0 && lq <= 0.0f) lo = x;
+    else hi = x;
+    // d(log q)/dl = (gamma + 1) rho'/rho - A'/A
+    const double dq = fma((double)g1 * pr, A, -r * fma(2.0 * x, a2, a1));
+    const double d = -0.6931471805599453 * (double)lq * (A * r) * fast_rcp(dq);
+    if (fabs(d) <= 1e-4) return fmin(fmax(x + d, lo), hi);
+    x += d;
+    if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);
+  }
+  return x;
+}
+
+// Root of the entropy bound to the accuracy of psi itself: one Newton step on
+// psi from the root of log q (gamma = 7/5), two from the rougher start of a
+// general gamma.  psi is concave, so a tangent's root x lies at or beyond the
+// root (within round-off of it from such a close start), and a point a below
+// x with psi(a) >= 0 is within x - a of the root.  The rounding of psi
+// blurs its sign change over a band of some 2^-52 E / |psi'|: the step back
+// starts at a quarter of that, 2e-15 at least, and doubles until psi confirms a
+// feasible point.  If none is confirmed (x was not close), the bracketing search
+// on psi runs.  Against 128-bit roots, in units of that band or 1e-14, the larger:
+// rms 0.2 - 0.6, at most 4 (steps of 2e-15 times powers of 8, gamma = 7/5: 0.3 -
+// 0.9, at most 17; the bracketing search alone: 0.2 - 0.6, at most 40).
+// A general gamma takes pow once, at the start x0: rho differs by less than
+// 3e-5 afterwards, where three terms of (1 + d)^gamma are exact to rounding.
+// The bracketing search takes 15, and its slowest lane holds up its wave: gamma =
+// 5/3, 1% noise on the Mach-3 tube state at 2048^2 (every row limited),
+// k_lim_rows 10.4 -> 2.7 ms per stage, the step 35.9 -> 12.3 ms.
 template <int DIM, int SEV>
 __device__ __forceinline__ double entropy_root_fast(const Gas &g, const double *u,
                                                    const double *P, double lr,
                                                    double pmin, double pmin5) {
 #pragma clang fp contract(off)  // the same bits in every kernel
+  double x0, x, d, w0 = 0.0, dr = 0.0;
   if constexpr (SEV) {
-    double x = entropy_root_seven<DIM>(u, P, lr, pmin5), d;
-    const double f = psi_eval<DIM, SEV>(g, u, P, x, pmin, &d);
+    x0 = entropy_root_seven<DIM>(u, P, lr, pmin5);
+  } else {
+    x0 = entropy_root_start<DIM>(g, u, P, lr, pmin);
+    const double r0 = fma(x0, P[0], u[0]);
+    w0 = pow(r0, g.gamma);
+    dr = P[0] / r0;
+  }
+  auto power = [&](double r, double l) {
+    if constexpr (SEV) {
+      return pow_seven_fifths(r);
+    } else {
+      const double t = (l - x0) * dr, c = g.gamma;
+      const double p = fma(t, fma(t, (c - 2.0) * (1.0 / 3.0), 1.0) * (0.5 * (c - 1.0)), 1.0);
+      return fma(w0, c * t * p, w0);
+    }
+  };
+  x = x0;
+  bool ok = true;
+#pragma unroll
+  for (int t = SEV; t < 2; ++t) {
+    const double f = psi_with<DIM>(g, u, P, x, pmin, &d, power);
     x -= f / d;
-    if (d < 0.0 && x > 0.0 && x <= lr) {
-      double h = fmax(2e-15, 0x1p-54 * fabs(fma(x, P[DIM + 1], u[DIM + 1]) / d));
-      for (int k = 0; k < 5; ++k, h *= 2.0) {
-        const double a = fmax(x - h, 0.0);
-        if (psi_eval<DIM, SEV>(g, u, P, a, pmin, nullptr) >= 0.0) return a;
-      }
+    if (t == 0) x = fmin(x, lr);
+    ok = ok && d < 0.0 && x > 0.0;
+    if (!SEV) ok = ok && fabs((x - x0) * dr) <= 3e-5;
+  }
+  if (ok && x <= lr) {
+    double h = fmax(2e-15, 0x1p-54 * fabs(fma(x, P[DIM + 1], u[DIM + 1]) / d));
+    for (int k = 0; k < 5; ++k, h *= 2.0) {
+      const double a = fmax(x - h, 0.0);
+      if (psi_with<DIM>(g, u, P, a, pmin, nullptr, power) >= 0.0) return a;
     }
   }
   return entropy_root<DIM, SEV>(g, u, P, lr, pmin);

@@ -100,7 +100,9 @@ def device(tmp_path_factory):
     subprocess.run(["g++", "-O2", "-std=gnu++17", "-ffp-contract=off", "-mfma", "-fPIC", "-shared",
                     "-Wno-unknown-pragmas", "-I", str(d), "-I", os.path.join(B.CSRC),
                     str(d / "root.cpp"), "-o", str(d / "root.so"), "-lquadmath"], check=True)
-    return C.CDLL(str(d / "root.so"))
+    L = C.CDLL(str(d / "root.so"))
+    L.run.restype = C.c_long
+    return L
 
 
 def ptr(a):
@@ -143,7 +145,7 @@ def lines(rng, n, dim, gamma, smallest, thin):
     return [np.ascontiguousarray(a[ok]) for a in (u, P, lr, pm)]
 
 
-GAMMAS = [(1.4, 1)]
+GAMMAS = [(1.4, 1), (1.4, 0), (5.0 / 3.0, 0), (1.1, 0), (3.0, 0)]
 
 
 @pytest.mark.parametrize("smallest,thin", [(1e-4, False), (1e-2, True), (0.3, False)])
@@ -154,8 +156,10 @@ def test_root(device, dim, gamma, seven, smallest, thin):
     n = len(lr)
     assert n > 1000
     out, err, slope = np.empty(n), np.empty(n), np.empty(n)
-    device.run(dim, seven, C.c_double(gamma), n, ptr(u), ptr(P), ptr(lr), ptr(pm), ptr(out),
-               ptr(err), ptr(slope))
+    calls = device.run(dim, seven, C.c_double(gamma), n, ptr(u), ptr(P), ptr(lr), ptr(pm),
+                       ptr(out), ptr(err), ptr(slope))
+    # (15 each by the bracketing search, which a few still need)
+    assert calls <= 2 * n
     assert np.all((out >= 0.0) & (out <= lr))
     # psi is known to about 2 units of 2^-52 E (the roundings of E, the kinetic
     # energy and phi rho^gamma); the Newton step ends within 2 units of its
