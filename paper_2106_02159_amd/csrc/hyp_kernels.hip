@@ -3,6 +3,7 @@
 #include "hyp_kernels.hpp"
 
 #include "line_sweep.hpp"
+#include "row_lists.hpp"
 
 #include <algorithm>
 #include <climits>
@@ -1208,7 +1209,8 @@ __device__ __forceinline__ void lo_lines(const DevGraphT<LT> &G, const StageArgs
 template <int DIM, typename LT>
 __global__ __launch_bounds__(kBlock) void k_lo(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
   clear_lists(A, row_id() == 0);
-  if (DIM == 3 && blockIdx.x == 0 && threadIdx.x < 2 * 64) A.q2[8 * threadIdx.x] = 0;
+  // the limiter's counters: 2D the lists' lengths (row_lists.hpp), 3D the roots
+  if (blockIdx.x == 0 && threadIdx.x < (DIM == 2 ? 64 : 2 * 64)) A.q2[8 * threadIdx.x] = 0;
   const uint32_t ns = spec_blocks<DIM>(G);
   if (blockIdx.x < ns) {
     lo_spec<DIM>(G, A, g);
@@ -1667,14 +1669,15 @@ __global__ __launch_bounds__(kBlock) void k_lim2(DevGraphT<LT> G, StageArgsT<LT>
 //                 the step to l = 1 stays inside the bounds), stores that sum
 //                 and a mask of the slots where it does not;
 //   k_lim_done    finishes the rows whose own and neighbours' masks are clear,
-//                 and marks the others (one bit per row);
+//                 and lists the others (row_lists.hpp);
 //   k_lim_rows    runs both limiter passes, roots included, for the marked
 //                 rows, 8 lanes (the 8 pairs) to a row;
 //   k_fin_rows    adds the pass-2 part of those that have one, 8 lanes to a
 //                 row again.
-// Marked rows come in long runs (a front along x marks whole lines), so a
-// workgroup of k_lim_rows takes slices of 64 rows that lie apart; a wave that
-// worked through its own slice had up to 8 rounds of 8 rows, 13 us each.
+// Marked rows come in long runs, so the waves of k_lim_rows and k_fin_rows take
+// equal parts of the list; a wave that worked through its own slice of 64 rows
+// had up to 8 rounds of 8 rows, 13 us each, and workgroups with fixed slices all
+// over the mesh lined up with fronts.
 // Against one sweep that gathered every neighbour slot by slot, kept P for
 // pass 2, and listed the entries with a root for two further kernels (FP64,
 // limiter and final update of a stage): 2.61 -> 1.48 ms at 4096^2, 0.27 ->
@@ -1999,10 +2002,36 @@ __device__ __forceinline__ void lim_pairs(const DevGraphT<LT> &G, const StageArg
   }
 }
 
-// Finishes the interior rows without a limited pair; A.todo: the others, a
-// bit each per slice of 64 rows.
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t c, uint32_t lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(c, d);
+    if ((int)lane >= d) c += o;
+  }
+  return c;
+}
+
+// Workgroups of k_lim_rows beside those of the listed rows: two per CU (what
+// fits), or one to 64 rows of a small mesh.
+__host__ __device__ __forceinline__ uint32_t lim_groups(int64_t N) {
+  const int64_t sl = (N + 63) / 64;
+  return (uint32_t)(sl < 512 ? sl : 512);
+}
+__host__ __device__ __forceinline__ uint32_t row_blocks(int64_t N) {
+  return (uint32_t)((N + kListRows - 1) / kListRows);
+}
+__host__ __device__ __forceinline__ uint32_t spec_groups(int nsrow) {
+  return (uint32_t)(nsrow + 63) / 64;
+}
+// A.q2: the lists' lengths, then (KEEP) the root counts of k_lim_rows'
+// workgroups.
+constexpr uint32_t kRootWords = kMaxLists * kListStep;
+
+// Finishes the interior rows without a limited pair and lists the others in A.q.
 template <typename LT>
 __global__ __launch_bounds__(kBlock) void k_lim_done(DevGraphT<LT> G, StageArgsT<LT> A) {
+  __shared__ uint32_t cnt[kBlock / 64], at;
   const int64_t N = G.N, r0 = (int64_t)blockIdx.x * kBlock;
   const uint32_t tid = threadIdx.x;
   const int lane = tid & 63;
@@ -2031,101 +2060,84 @@ __global__ __launch_bounds__(kBlock) void k_lim_done(DevGraphT<LT> G, StageArgsT
     A.nzm[r0 + tid] = 0;
     if (lim == 0) finish<2>(G, A, r0 + tid, u1);
   }
-  const uint64_t todo = __ballot(act && lim != 0);
-  if (lane == 0 && r0 + tid < N) A.todo[(r0 + tid) >> 6] = todo;
+  const bool marked = act && lim != 0;
+  const uint64_t w = __ballot(marked);
+  if (lane == 0) cnt[tid >> 6] = (uint32_t)__builtin_popcountll(w);
+  __syncthreads();
+  uint32_t total = 0, before = 0;
+#pragma unroll
+  for (uint32_t v = 0; v < kBlock / 64; ++v) {
+    before += v < (tid >> 6) ? cnt[v] : 0;
+    total += cnt[v];
+  }
+  if (total == 0) return;
+  const RowLists rl(row_blocks(N));
+  const uint32_t list = rl.list_of(blockIdx.x);
+  if (tid == 0) at = atomicAdd(&A.q2[kListStep * list], total);
+  __syncthreads();
+  if (marked)
+    A.q[(int64_t)list * rl.room + at + before +
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32),
+                                  __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0))] =
+        (uint32_t)(r0 + tid);
 }
 
-// Workgroups of k_lim_rows beside those of the listed rows: two per CU (what
-// fits), or as many as keep each at 128 slices: one of every n, at a place
-// that moves on by kSkew each time.  Without the skew, where n slices are a
-// whole number of mesh lines, a workgroup had the same columns of every line,
-// and the few with a front along y had all of it (4096^2, steps 4 to 23 from
-// four quadrants: 1.51 ms at 0.4 waves per SIMD on average, now 0.22 ms, and
-// k_fin_rows 0.35 -> 0.06 ms; FP64 step 14.06 -> 9.25 ms).
-constexpr uint32_t kSkew = 37;
-constexpr int kSlices = 128;
-__host__ __device__ __forceinline__ uint32_t lim_groups(int64_t N) {
-  const int64_t sl = (N + 63) / 64, n = (sl + kSlices - 1) / kSlices;
-  return (uint32_t)(n > 512 ? n : sl < 512 ? sl : 512);
-}
-__host__ __device__ __forceinline__ uint32_t lim_slices(int64_t N) {
-  const uint32_t n = lim_groups(N);
-  return (uint32_t)(((N + 63) / 64 + n - 1) / n);
-}
-// Slice t of workgroup b.
-__device__ __forceinline__ uint32_t lim_slice(uint32_t b, uint32_t t, uint32_t n) {
-  return t * n + (b + kSkew * t) % n;
-}
-__host__ __device__ __forceinline__ uint32_t spec_groups(int nsrow) {
-  return (uint32_t)(nsrow + 63) / 64;
+// f(row, ok) for the rows of this wave, 8 at a time (a lane's row is lane / 8's;
+// lanes with ok = false have another one's): of G.srow in the first `ns`
+// workgroups, of the lists in the others.
+template <typename LT, class F>
+__device__ __forceinline__ void wave_rows(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                          uint32_t ns, F &&f) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool front = blockIdx.x < ns;
+  uint32_t lists = 1, room = 0, each = 64, step = 1, len = (uint32_t)G.nsrow, longest = len;
+  const uint32_t *q = (const uint32_t *)G.srow;
+  if (!front) {
+    const RowLists rl(row_blocks(G.N));
+    const uint32_t groups = lim_groups(G.N);
+    lists = rl.lists;
+    room = rl.room;
+    q = A.q;
+    step = groups;
+    len = lane < lists ? A.q2[kListStep * lane] : 0;
+    longest = len;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) longest = max(longest, (uint32_t)__shfl_xor((int)longest, d));
+    longest = __builtin_amdgcn_readfirstlane(longest);
+    each = part_rows(longest, lists, groups);
+  }
+  if (8 * wave >= each) return;
+  for (uint32_t p = front ? blockIdx.x : blockIdx.x - ns;; p += step) {
+    const uint32_t l = p & (lists - 1), at = p / lists * each;
+    if (at >= longest) return;
+    const uint32_t n = __builtin_amdgcn_readlane(len, l), t0 = at + 8 * wave;
+    if (t0 < n) {
+      const uint32_t t = t0 + (lane >> 3);
+      f(q[(int64_t)l * room + min(t, n - 1)], t < n);
+    }
+    if (front) return;
+  }
 }
 
-// The listed rows (front workgroups), and the marked rows of the workgroup's
-// slices, 64 rows at a time.  Their list goes to A.q for k_fin_rows, its
-// length to A.q2.
+// The listed rows (G.srow, front workgroups), and the marked rows, 8 to a wave.
 template <int SEV, bool KEEP, typename LT>
 __global__ __launch_bounds__(kWide) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_lim_rows(
     DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
   __shared__ double nb_words[9][kWide];
-  __shared__ uint32_t list[kSlices * 64];
-  __shared__ uint64_t bits[kSlices];
-  __shared__ uint32_t first[kSlices + 1], roots[2];
+  __shared__ uint32_t roots[2];
   const uint32_t ns = spec_groups(G.nsrow), tid = threadIdx.x;
-  const uint32_t lane = tid & 63, wave = tid >> 6;
-  const bool front = blockIdx.x < ns;
-  uint32_t n = 64;
-  if (KEEP && tid < 2) roots[tid] = 0;
-  if (front) {
-    if (tid < 64) list[tid] = G.srow[min((int)(blockIdx.x * 64 + tid), G.nsrow - 1)];
-    n = min(64u, (uint32_t)G.nsrow - blockIdx.x * 64);
-    __syncthreads();
-  } else {
-    const uint32_t b = blockIdx.x - ns, stride = lim_groups(G.N), most = lim_slices(G.N);
-    const uint32_t slices = (uint32_t)((G.N + 63) / 64);
-    if (wave == 0) {  // bits and running counts of the slices
-      uint32_t sum = 0;
-#pragma unroll
-      for (uint32_t t0 = 0; t0 < kSlices; t0 += 64) {
-        const uint32_t t = t0 + lane, sl = lim_slice(b, t, stride);
-        const uint64_t w = t < most && sl < slices ? A.todo[sl] : 0;
-        uint32_t c = (uint32_t)__builtin_popcountll(w);
-        const uint32_t own = c;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-          const uint32_t o = __shfl_up(c, d);
-          if ((int)lane >= d) c += o;
-        }
-        bits[t] = w;
-        first[t] = sum + c - own;
-        sum += __shfl(c, 63);
-      }
-      if (lane == 0) {
-        first[kSlices] = sum;
-        A.q2[b] = sum;
-      }
-    }
-    __syncthreads();
-    n = first[kSlices];
-    for (uint32_t t = wave; t < most; t += kWide / 64) {
-      const uint64_t w = bits[t];
-      if ((w >> lane) & 1u) {
-        const uint32_t at = first[t] + __builtin_amdgcn_mbcnt_hi(
-                                (uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0));
-        const uint32_t row = lim_slice(b, t, stride) * 64 + lane;
-        list[at] = row;
-        A.q[b * (most * 64) + at] = row;
-      }
-    }
+  const uint32_t lane = tid & 63;
+  if constexpr (KEEP) {
+    if (tid < 2) roots[tid] = 0;
     __syncthreads();
   }
-  for (uint32_t t0 = 0; t0 < n; t0 += 64) {
-    const uint32_t t = t0 + (tid >> 3);
-    lim_pairs<SEV, KEEP, LT>(G, A, g, list[min(t, n - 1)], lane & 7, lane & ~7u, t < n,
-                              roots, &nb_words[0][tid]);
-  }
+  wave_rows(G, A, ns, [&](uint32_t row, bool ok) __attribute__((always_inline)) {
+    lim_pairs<SEV, KEEP, LT>(G, A, g, row, lane & 7, lane & ~7u, ok, roots, &nb_words[0][tid]);
+  });
   if constexpr (KEEP) {
     __syncthreads();
-    if (tid < 2) A.q2[lim_groups(G.N) + 2 * blockIdx.x + tid] = roots[tid];
+    if (tid < 2) A.q2[kRootWords + 2 * blockIdx.x + tid] = roots[tid];
   }
 }
 
@@ -2176,19 +2188,14 @@ __global__ __launch_bounds__(kWide) void k_fin_rows(DevGraphT<LT> G, StageArgsT<
     // root entries of both passes: wave p sums pass p + 1's counts
     const uint32_t p = tid >> 6;
     uint32_t c = 0;
-    for (uint32_t t = lane; t < gridDim.x; t += 64) c += A.q2[lim_groups(G.N) + 2 * t + p];
+    for (uint32_t t = lane; t < gridDim.x; t += 64) c += A.q2[kRootWords + 2 * t + p];
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
     if (lane == 0) A.qcnt[p] = c;
   }
-  const bool front = blockIdx.x < ns;
-  const uint32_t b = front ? blockIdx.x : blockIdx.x - ns;
-  const uint32_t n = front ? min(64u, (uint32_t)G.nsrow - b * 64) : A.q2[b];
-  const uint32_t first = b * (front ? 64u : lim_slices(G.N) * 64);
-  for (uint32_t t0 = 0; t0 < n; t0 += 64) {
-    const uint32_t t = t0 + (tid >> 3), at = first + min(t, n - 1);
-    fin_pairs<LT>(G, A, front ? (uint32_t)G.srow[at] : A.q[at], lane & 7, lane & ~7, t < n);
-  }
+  wave_rows(G, A, ns, [&](uint32_t row, bool ok) __attribute__((always_inline)) {
+    fin_pairs<LT>(G, A, row, lane & 7, lane & ~7, ok);
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -2212,16 +2219,6 @@ __global__ __launch_bounds__(kWide) void k_fin_rows(DevGraphT<LT> G, StageArgsT<
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-}
-
-// Inclusive sum over the lanes of a wave.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t c, uint32_t lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t o = __shfl_up(c, d);
-    if ((int)lane >= d) c += o;
-  }
-  return c;
 }
 
 // Workgroups of the listed rows, 64 to a wave.

@@ -19,9 +19,9 @@
 //   two limiter passes:
 //   k_lim_first    P_ij (Sec. 3.3), U^L + lambda_i sum P and the mask of the
 //                  pairs whose pass-1 line search does not return 1
-//   2D: k_lim_done finishes the rows without such a pair, k_lim_rows runs both
-//                  passes (roots of the entropy bound included) for the others,
-//                  8 lanes each, k_fin_rows adds the pass-2 part
+//   2D: k_lim_done finishes the rows without such a pair and lists the others,
+//                  k_lim_rows runs both passes (roots of the entropy bound
+//                  included) for them, 8 lanes each, k_fin_rows adds the pass-2 part
 //   3D: k_lim_entries runs both passes, a lane per limited entry, and finishes
 //                  the rows without a pass-2 part, k_fin_entries the others
 //   one pass:
@@ -105,8 +105,9 @@ struct StageArgsT {
   uint32_t *q;
   uint32_t *qcnt;
   // the pass-2 work list q2 (W*Np entries; null: q, filled after q is emptied).
-  // Launched two-pass limiting lists no roots: 2D keeps the limited rows of
-  // its slices in q and their number in q2, 3D its spread root counters in q2
+  // Launched two-pass limiting lists no roots: 2D lists the limited rows in q
+  // (row_lists.hpp), with the lists' lengths and root counts in q2, 3D its spread
+  // root counters in q2
   uint32_t *q2 = nullptr;
   int *clear = nullptr;  // the status flags, where the stage starts by clearing them
   // per row, bit k set where the stored pass-2 product of slot k may be
@@ -115,9 +116,6 @@ struct StageArgsT {
   // per row, bit k set where the row's own pass-1 search of slot k does
   // not return 1 (k_lim_first); N entries
   uint32_t *lim = nullptr;
-  // 2D: per slice of 64 rows, a bit for each interior row with a pair that
-  // is limited (k_lim_done); Np / 64 entries
-  uint64_t *todo = nullptr;
   // keep l~, l~' of all entries and U^(1) of all rows (the last stage of
   // a step, and ns_fe_stage); otherwise only what the stage itself reads
   int keep = 1;

@@ -174,7 +174,6 @@ struct ns_solver {
   uint32_t *q = nullptr, *qcnt = nullptr;
   uint32_t *nzm = nullptr;  // 2D: slots with a pass-2 weight, per row
   uint32_t *lim = nullptr;  // 2D: slots limited by the row's own search
-  uint64_t *todo = nullptr;  // 2D: rows with a limited pair, a bit each
   // host copies of device scalars (pageable: no pinned allocation, whose
   // release would synchronize the whole device)
   int hflags[4] = {0, 0, 0, 0};
@@ -239,7 +238,6 @@ struct ns_solver {
     b.U1 = a.U1; b.partial = a.partial; b.tau = a.tau; b.flags = a.flags;
     b.sa = a.sa; b.sb = a.sb; b.check_cfl = a.check_cfl; b.q = a.q; b.qcnt = a.qcnt;
     b.q2 = a.q2; b.nzm = a.nzm; b.lim = a.lim; b.clear = a.clear;
-    b.todo = a.todo;
     b.seg = a.seg; b.mblk = a.mblk; b.nmem = a.nmem; b.check_low = a.check_low;
     b.keep = a.keep;
     b.alpha = alphaf; b.d = df; b.FH = FHf; b.lt1 = lt1f; b.lt2 = lt2f;
@@ -258,7 +256,6 @@ struct ns_solver {
     a.q2 = q + (int64_t)W * Np;  // the pass-2 list
     a.nzm = nzm;
     a.lim = lim;
-    a.todo = todo;
     a.seg = seg; a.mblk = mblk; a.nmem = nmem;
     a.keep = keep;
     return a;
@@ -874,7 +871,7 @@ int64_t footprint(const Layout &Lt, const ns_params *p) {
   b += 3 * nc * N * 8 + 4 * N * 8;                   // states, aux
   b += N * L + W * Np * L + nc * N * 8 + (nc + (dim == 3)) * N * L;  // alpha, d, U^L, F^H
   b += 3 * N * 8 + 2 * W * Np * L + nc * N * 8;      // bounds, l~ (2), U^(1)
-  b += 2 * N * 4 + Np / 8;                           // pass-2 weight and pass-1 masks, rows
+  b += 2 * N * 4;                                    // pass-2 weight and pass-1 masks
   b += nblocks * 8 + nm * (8 + 4 * 4 + 8);           // partial, tau, flags, time
   b += 2 * W * Np * 4 + 4 * 4;                       // root work lists
   b += nslip * 4 + dim * nslip * 8;                  // slip list
@@ -1025,7 +1022,6 @@ int create_impl(const Layout &Lt, const ns_params *p, void *stream, ns_solver **
   NS_ALLOC(s->U1, nc * N);
   NS_ALLOC(s->nzm, N);
   NS_ALLOC(s->lim, N);
-  NS_ALLOC(s->todo, Np / 64);
   NS_ALLOC(s->partial, nblocks);
   NS_ALLOC(s->tau, 3 * s->nmem);  // tau, then 4 flags, of every member
   s->flags = (int *)(s->tau + s->nmem);
