@@ -214,7 +214,11 @@ __device__ __forceinline__ global_ptr<T> edge_t(T *a, int64_t jb, int k, uint32_
 template <int DIM, typename LT>
 __host__ __device__ __forceinline__ uint32_t spec_blocks(const DevGraphT<LT> &G) {
   constexpr uint32_t per = (64 / (DIM == 2 ? 3 : 9)) * (kBlock / 64);
-  return ((uint32_t)G.nsrow + per - 1) / per;
+  return G.byrow ? 0 : ((uint32_t)G.nsrow + per - 1) / per;
+}
+// Workgroups of the listed rows, a lane each.
+__host__ __device__ __forceinline__ uint32_t spec_slices(int nsrow) {
+  return (uint32_t)(nsrow + kBlock - 1) / kBlock;
 }
 template <int DIM>
 struct SpecLane {
@@ -422,6 +426,7 @@ __device__ __forceinline__ void visc_line(const DevGraphT<LT> &G,
   for (int t = 0; t < 3; ++t) {
     const int k = 3 * l + t;
     const int32_t j = jv[k];
+    if (ANY && !__any(j >= 0)) continue;  // (absent entries add zeros)
     const int64_t js = j >= 0 ? j : i;
     double uj[NC];
     load_state<NC>(U, N, js, uj);
@@ -501,26 +506,27 @@ __device__ __forceinline__ void visc_spec(const DevGraphT<LT> &G,
   if (L.ok && L.line == 0) alpha[L.i] = alpha_of<IND, LT>(num, den, scl);
 }
 
-// Any row by one lane (the persistent steps): sums along the row as the line
-// sweep forms them if it is interior, line by line as visc_spec if not.
-template <int DIM, int SEV, typename LT>
+// Any row by one lane: sums along the row as the line sweep forms them if it is
+// interior, line by line as visc_spec if not.
+template <int DIM, int IND, int SEV, typename LT>
 __device__ __forceinline__ void visc_row(const DevGraphT<LT> &G,
                                          const double *__restrict__ U,
                                          const double *__restrict__ aux,
                                          LT *__restrict__ d, LT *__restrict__ alpha,
-                                         const Gas &g, BoxNbr<DIM> jv, int64_t i) {
-  const ViscRow<DIM, 0> R(G, U, aux, g, i);
+                                         const Gas &g, BoxNbr<DIM> jv, int64_t i,
+                                         bool store = true) {
+  const ViscRow<DIM, IND> R(G, U, aux, g, i);
   const bool in = jv.interior();
   double num = 0.0, den = 0.0, scl = 0.0, tn = 0.0, td = 0.0, ts = 0.0;
 #pragma unroll 1
   for (int l = 0; l < Cfg<DIM>::W / 3; ++l) {
-    visc_line<DIM, 0, SEV, true, LT>(G, U, aux, d, g, jv, i, R, l, true, num, den, scl);
+    visc_line<DIM, IND, SEV, true, LT>(G, U, aux, d, g, jv, i, R, l, store, num, den, scl);
     if (!in) {
       tn += num; td += den; ts += scl;
       num = den = scl = 0.0;
     }
   }
-  alpha[i] = in ? alpha_of<0, LT>(num, den, scl) : alpha_of<0, LT>(tn, td, ts);
+  if (store) alpha[i] = in ? alpha_of<IND, LT>(num, den, scl) : alpha_of<IND, LT>(tn, td, ts);
 }
 
 // The interior rows of row block blk, line by line (line_sweep.hpp).
@@ -807,6 +813,27 @@ __global__ __launch_bounds__(kBlock) void k_visc(DevGraphT<LT> G,
   }
 }
 
+// A lane's row where every row goes by itself (DevGraphT::byrow; lanes beyond
+// the last row repeat it without stores).
+template <int DIM>
+struct OwnRow {
+  int64_t i;
+  bool ok;
+  BoxNbr<DIM> nb;
+  template <typename LT>
+  __device__ __forceinline__ explicit OwnRow(const DevGraphT<LT> &G)
+      : i(min(row_id(), G.N - 1)), ok(row_id() < G.N), nb(block_nbr<DIM>(G, blockIdx.x, i)) {}
+};
+template <int DIM, int IND, int SEV, typename LT>
+__global__ __launch_bounds__(kBlock) void k_visc_rows(DevGraphT<LT> G,
+                                                      const double *__restrict__ U,
+                                                      const double *__restrict__ aux,
+                                                      LT *__restrict__ d,
+                                                      LT *__restrict__ alpha, Gas g) {
+  const OwnRow<DIM> r(G);
+  visc_row<DIM, IND, SEV, LT>(G, U, aux, d, alpha, g, r.nb, r.i, r.ok);
+}
+
 // ---------------------------------------------------------------------------
 // Time step: per-block min of m_i / (2 sum_{j != i} d_ij) = -m_i / (2 d_ii).
 // (every thread of the workgroup calls it: it ends in a workgroup reduction)
@@ -967,6 +994,14 @@ __device__ __forceinline__ void clear_lists(const StageArgsT<LT> &A, bool first)
   }
 }
 
+// The counters of the stage's limiter: k_lim1's list, 2D the lists' lengths
+// (row_lists.hpp), 3D the spread root counters.
+template <int DIM, typename LT>
+__device__ __forceinline__ void clear_counters(const StageArgsT<LT> &A) {
+  clear_lists(A, row_id() == 0);
+  if (blockIdx.x == 0 && threadIdx.x < (DIM == 2 ? 64 : 2 * 64)) A.q2[8 * threadIdx.x] = 0;
+}
+
 // The general path (see visc_line): adds the entries of line l of row i;
 // csum is the sum of c_ij, the diagonal entry's flux goes to F^H directly.
 template <int DIM, bool ANY, typename LT>
@@ -977,6 +1012,10 @@ __device__ __forceinline__ void lo_line(const DevGraphT<LT> &G, const StageArgsT
 #pragma clang fp contract(off)  // the same bits in every kernel
   constexpr int NC = DIM + 2, ALL = (1 << DIM) - 1, C = Cfg<DIM>::W / 2;
   const int64_t N = G.N;
+  if (ANY) {  // (absent entries add zeros)
+    const bool any = jv[3 * l] >= 0 || jv[3 * l + 1] >= 0 || jv[3 * l + 2] >= 0;
+    if (!__any(any)) return;
+  }
   double uj[3][NC], phij[3], alj[3], dl[3];
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
@@ -1071,10 +1110,11 @@ __device__ __forceinline__ void lo_spec(const DevGraphT<LT> &G, const StageArgsT
   }
 }
 
-// Any row by one lane (see visc_row).
+// A row by one lane (see visc_row).
 template <int DIM, typename LT>
 __device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
-                                       const Gas &g, BoxNbr<DIM> jv, int64_t i) {
+                                       const Gas &g, BoxNbr<DIM> jv, int64_t i,
+                                       bool store = true) {
   constexpr int NC = DIM + 2;
   double ui[NC], vi[DIM], pi, csum[DIM], tc[DIM];
   load_state<NC>(A.U, G.N, i, ui);
@@ -1113,7 +1153,13 @@ __device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<
     lo_own_flux<DIM>(ui, vi, pi, tc, T);
     S = T;
   }
-  lo_store<DIM>(G, A, i, mem, A.tau[mem], ui, al, S);
+  if (store) lo_store<DIM>(G, A, i, mem, A.tau[mem], ui, al, S);
+}
+template <int DIM, typename LT>
+__global__ __launch_bounds__(kBlock) void k_lo_rows(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
+  clear_counters<DIM>(A);
+  const OwnRow<DIM> r(G);
+  lo_row<DIM>(G, A, g, r.nb, r.i, r.ok);
 }
 
 // The interior rows of row block blk, line by line (line_sweep.hpp).
@@ -1208,9 +1254,7 @@ __device__ __forceinline__ void lo_lines(const DevGraphT<LT> &G, const StageArgs
 
 template <int DIM, typename LT>
 __global__ __launch_bounds__(kBlock) void k_lo(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
-  clear_lists(A, row_id() == 0);
-  // the limiter's counters: 2D the lists' lengths (row_lists.hpp), 3D the roots
-  if (blockIdx.x == 0 && threadIdx.x < (DIM == 2 ? 64 : 2 * 64)) A.q2[8 * threadIdx.x] = 0;
+  clear_counters<DIM>(A);
   const uint32_t ns = spec_blocks<DIM>(G);
   if (blockIdx.x < ns) {
     lo_spec<DIM>(G, A, g);
@@ -1720,7 +1764,6 @@ __device__ __forceinline__ void line_flux(const StageArgsT<LT> &A, int64_t N, in
   }
 }
 
-constexpr uint32_t kSpecRow = 0x80000000u;  // bit of A.lim: a listed row
 constexpr int kWide = 512;                  // lanes: 64 rows of 8 pairs
 
 template <int DIM, int SEV, bool KEEP, typename LT>
@@ -1874,8 +1917,80 @@ __device__ __forceinline__ void lim_first_spec(const DevGraphT<LT> &G, const Sta
     for (int q = 0; q < NC; ++q) part[q] = ul[q] + L.sum(part[q]);
   }
   if (L.ok && L.line == 0) {
-    A.lim[i] = mask | kSpecRow;
+    A.lim[i] = mask;
     if constexpr (DIM == 3) store_state<NC>(A.U1, N, i, part);
+  }
+}
+
+// Every row by itself: the sum in the order of lim_first_lines and, 3D, for a
+// row that is not interior of lim_first_spec.
+template <int DIM, int SEV, bool KEEP, typename LT>
+__global__ __launch_bounds__(kBlock) void k_lim_first_rows(DevGraphT<LT> G, StageArgsT<LT> A,
+                                                           Gas g) {
+#pragma clang fp contract(off)
+  constexpr int NC = DIM + 2, C = Cfg<DIM>::W / 2;
+  const OwnRow<DIM> r(G);
+  const int64_t N = G.N, i = r.i;
+  const BoxNbr<DIM> &jv = r.nb;
+  const bool serial = DIM == 2 || jv.interior();
+  RowCtx<DIM> R;
+  load_row<DIM>(G, A, i, A.tau[member(A, i)], R);
+  double ul[NC], u1[NC];
+  load_state<NC>(A.UL, N, i, ul);
+  const Bounds b = load_bounds(A, N, i);
+  const double lam = 1.0 / G.lfac[i];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) u1[q] = serial ? ul[q] : 0.0;
+  uint32_t mask = 0;
+#pragma unroll 1
+  for (int l = 0; l < Cfg<DIM>::W / 3; ++l) {
+    int32_t j[3];
+    bool any = false;
+    PIn<DIM> x[3];
+    double part[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) part[q] = 0.0;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      j[t] = 3 * l + t != C ? jv[3 * l + t] : -1;
+      any = any || j[t] >= 0;
+    }
+    if (!__any(any)) continue;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      gather_P<DIM>(G, A, eidx<DIM>(3 * l + t, i), j[t] >= 0 ? j[t] : i, jv.mass(3 * l + t),
+                    x[t]);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int k = 3 * l + t;
+      double P[NC];
+      make_P<DIM>(R, x[t], P);
+      if (j[t] < 0) continue;
+      if (!limit_is_one<DIM, SEV>(g, ul, P, b)) mask |= 1u << k;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const double t = lam * P[q];
+        if (serial) u1[q] += t;
+        else part[q] += t;
+      }
+      if (KEEP && r.ok) {
+        A.lt1[eidx<DIM>(k, i)] = LT(1);
+        A.lt2[eidx<DIM>(k, i)] = LT(0);
+      }
+    }
+    if (!serial) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) u1[q] += part[q];
+    }
+  }
+  if (r.ok) {
+    if constexpr (DIM == 3) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) u1[q] = serial ? u1[q] : ul[q] + u1[q];
+    }
+    store_state<NC>(A.U1, N, i, u1);
+    A.lim[i] = mask;
   }
 }
 
@@ -2021,17 +2136,44 @@ __host__ __device__ __forceinline__ uint32_t lim_groups(int64_t N) {
 __host__ __device__ __forceinline__ uint32_t row_blocks(int64_t N) {
   return (uint32_t)((N + kListRows - 1) / kListRows);
 }
-__host__ __device__ __forceinline__ uint32_t spec_groups(int nsrow) {
-  return (uint32_t)(nsrow + 63) / 64;
+template <typename LT>
+__host__ __device__ __forceinline__ uint32_t spec_groups(const DevGraphT<LT> &G) {
+  return G.byrow ? 0 : (uint32_t)(G.nsrow + 63) / 64;
 }
 // A.q2: the lists' lengths, then (KEEP) the root counts of k_lim_rows'
 // workgroups.
 constexpr uint32_t kRootWords = kMaxLists * kListStep;
 
-// Finishes the interior rows without a limited pair and lists the others in A.q.
+// Appends the marked lanes' rows of a workgroup to its list in A.q (every thread
+// calls it).
+template <typename LT>
+__device__ __forceinline__ void list_rows(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
+                                          int64_t i, bool marked) {
+  __shared__ uint32_t cnt[kBlock / 64], at;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t w = __ballot(marked);
+  if ((tid & 63) == 0) cnt[tid >> 6] = (uint32_t)__builtin_popcountll(w);
+  __syncthreads();
+  uint32_t total = 0, before = 0;
+#pragma unroll
+  for (uint32_t v = 0; v < kBlock / 64; ++v) {
+    before += v < (tid >> 6) ? cnt[v] : 0;
+    total += cnt[v];
+  }
+  if (total == 0) return;
+  const RowLists rl(row_blocks(G.N));
+  const uint32_t list = rl.list_of(blockIdx.x);
+  if (tid == 0) at = atomicAdd(&A.q2[kListStep * list], total);
+  __syncthreads();
+  if (marked)
+    A.q[(int64_t)list * rl.room + at + before +
+        __builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32),
+                                  __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0))] = (uint32_t)i;
+}
+
+// Finishes the interior rows without a limited pair and lists the others.
 template <typename LT>
 __global__ __launch_bounds__(kBlock) void k_lim_done(DevGraphT<LT> G, StageArgsT<LT> A) {
-  __shared__ uint32_t cnt[kBlock / 64], at;
   const int64_t N = G.N, r0 = (int64_t)blockIdx.x * kBlock;
   const uint32_t tid = threadIdx.x;
   const int lane = tid & 63;
@@ -2060,26 +2202,28 @@ __global__ __launch_bounds__(kBlock) void k_lim_done(DevGraphT<LT> G, StageArgsT
     A.nzm[r0 + tid] = 0;
     if (lim == 0) finish<2>(G, A, r0 + tid, u1);
   }
-  const bool marked = act && lim != 0;
-  const uint64_t w = __ballot(marked);
-  if (lane == 0) cnt[tid >> 6] = (uint32_t)__builtin_popcountll(w);
-  __syncthreads();
-  uint32_t total = 0, before = 0;
+  list_rows(G, A, r0 + tid, act && lim != 0);
+}
+
+// Every row by itself.
+template <typename LT>
+__global__ __launch_bounds__(kBlock) void k_lim_done_rows(DevGraphT<LT> G, StageArgsT<LT> A) {
+  const OwnRow<2> r(G);
+  uint32_t lim = A.lim[r.i];
 #pragma unroll
-  for (uint32_t v = 0; v < kBlock / 64; ++v) {
-    before += v < (tid >> 6) ? cnt[v] : 0;
-    total += cnt[v];
+  for (int k = 0; k < 9; ++k) {
+    const int32_t j = r.nb[k];
+    if (k != 4) lim |= j >= 0 ? (A.lim[j >= 0 ? j : r.i] >> (8 - k)) & 1u : 0u;
   }
-  if (total == 0) return;
-  const RowLists rl(row_blocks(N));
-  const uint32_t list = rl.list_of(blockIdx.x);
-  if (tid == 0) at = atomicAdd(&A.q2[kListStep * list], total);
-  __syncthreads();
-  if (marked)
-    A.q[(int64_t)list * rl.room + at + before +
-        __builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32),
-                                  __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0))] =
-        (uint32_t)(r0 + tid);
+  if (r.ok) {
+    A.nzm[r.i] = 0;
+    if (lim == 0) {
+      double u1[4];
+      load_state<4>(A.U1, G.N, r.i, u1);
+      finish<2>(G, A, r.i, u1);
+    }
+  }
+  list_rows(G, A, r.i, r.ok && lim != 0);
 }
 
 // f(row, ok) for the rows of this wave, 8 at a time (a lane's row is lane / 8's;
@@ -2120,13 +2264,14 @@ __device__ __forceinline__ void wave_rows(const DevGraphT<LT> &G, const StageArg
   }
 }
 
-// The listed rows (G.srow, front workgroups), and the marked rows, 8 to a wave.
+// The listed rows (front workgroups; none where every row goes by itself), and
+// the marked rows, 8 to a wave.
 template <int SEV, bool KEEP, typename LT>
 __global__ __launch_bounds__(kWide) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_lim_rows(
     DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
   __shared__ double nb_words[9][kWide];
   __shared__ uint32_t roots[2];
-  const uint32_t ns = spec_groups(G.nsrow), tid = threadIdx.x;
+  const uint32_t ns = spec_groups(G), tid = threadIdx.x;
   const uint32_t lane = tid & 63;
   if constexpr (KEEP) {
     if (tid < 2) roots[tid] = 0;
@@ -2182,7 +2327,7 @@ __device__ __forceinline__ void fin_pairs(const DevGraphT<LT> &G, const StageArg
 
 template <typename LT>
 __global__ __launch_bounds__(kWide) void k_fin_rows(DevGraphT<LT> G, StageArgsT<LT> A) {
-  const uint32_t ns = spec_groups(G.nsrow), tid = threadIdx.x;
+  const uint32_t ns = spec_groups(G), tid = threadIdx.x;
   const int lane = tid & 63;
   if (A.keep && blockIdx.x == 0 && tid < 128) {
     // root entries of both passes: wave p sums pass p + 1's counts
@@ -2221,10 +2366,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Workgroups of the listed rows, 64 to a wave.
-__host__ __device__ __forceinline__ uint32_t spec_slices(int nsrow) {
-  return (uint32_t)(nsrow + kBlock - 1) / kBlock;
-}
 // Counters of entries with a root (KEEP): kRootCnt of each pass, 8 words apart
 // in A.q2, cleared by k_lo and summed by k_fin_entries (a single one would
 // serialise the workgroups).
@@ -2310,14 +2451,14 @@ k_lim_entries(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
     const int t = (int)(blockIdx.x * kBlock + tid);
     act = t < G.nsrow;
     i = G.srow[min(t, G.nsrow - 1)];
-    lim = (A.lim[i] & 0x7ffffffu) | listed_bits(G, A.lim, i);
+    lim = A.lim[i] | listed_bits(G, A.lim, i);
   } else {
     const uint32_t blk = blockIdx.x - ns;
     const int64_t r0 = (int64_t)blk * kBlock;
     geo = block_geo(G, blk);
     act = line_row(G, r0 + tid);
     i = min(r0 + (int64_t)tid, N - 1);
-    lim = (A.lim[i] & 0x7ffffffu) |
+    lim = A.lim[i] |
           line_bits(geo, A.lim, r0, N, tid);
   }
   if (!act) lim = 0;
@@ -3230,7 +3371,7 @@ __global__ __launch_bounds__(kBlock) void k_persist(DevGraphT<LT> G, PersistArgs
       case PP_PRIM: prim_row<DIM>(G.N, A.U, A.aux, g, i); break;
       case PP_VISC:
         if (i < G.N)
-          visc_row<DIM, SEV, LT>(G, A.U, A.aux, A.d, A.alpha, g, block_nbr<DIM>(G, blk, i), i);
+          visc_row<DIM, 0, SEV, LT>(G, A.U, A.aux, A.d, A.alpha, g, block_nbr<DIM>(G, blk, i), i);
         break;
       case PP_DTP: dt_partial_blk<DIM, LT>(G, A.d, A.partial, blk, i); break;
       case PP_DTF:
@@ -3298,16 +3439,20 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                            A.aux, A.d, A.alpha, gas));
     }
   }
-  if (f32) {
-  } else if (indicator == 0)
-    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 0, SEV, LT>), lgrid, block, 0, s, G,
-                                         A.U, A.aux, A.d, A.alpha, gas));
-  else if (indicator == 1)
-    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 1, SEV, LT>), lgrid, block, 0, s, G,
-                                         A.U, A.aux, A.d, A.alpha, gas));
-  else
-    NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), lgrid, block, 0, s, G,
-                                         A.U, A.aux, A.d, A.alpha, gas));
+  if (!f32) {
+    auto visc = [&](auto ind) {
+      constexpr int IND = decltype(ind)::value;
+      if (G.byrow)
+        NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc_rows<DIM, IND, SEV, LT>), grid, block, 0, s,
+                                             G, A.U, A.aux, A.d, A.alpha, gas));
+      else
+        NS_LAUNCH("visc", hipLaunchKernelGGL((k_visc<DIM, IND, SEV, LT>), lgrid, block, 0, s, G,
+                                             A.U, A.aux, A.d, A.alpha, gas));
+    };
+    if (indicator == 0) visc(std::integral_constant<int, 0>{});
+    else if (indicator == 1) visc(std::integral_constant<int, 1>{});
+    else visc(std::integral_constant<int, 2>{});
+  }
   if (auto_dt) {
     NS_LAUNCH("dt_partial", hipLaunchKernelGGL((k_dt_partial<DIM, LT>), grid, block, 0, s,
                                                G, A.d, A.partial));
@@ -3319,7 +3464,10 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
       NS_LAUNCH("dt_final", hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(1024), 0, s,
                                                A.partial, (int64_t)grid.x, cfl, A.tau));
   }
-  NS_LAUNCH("lo", hipLaunchKernelGGL((k_lo<DIM, LT>), lgrid, block, 0, s, G, A, gas));
+  if (G.byrow)
+    NS_LAUNCH("lo", hipLaunchKernelGGL((k_lo_rows<DIM, LT>), grid, block, 0, s, G, A, gas));
+  else
+    NS_LAUNCH("lo", hipLaunchKernelGGL((k_lo<DIM, LT>), lgrid, block, 0, s, G, A, gas));
   if (limiter == 1) {
     NS_LAUNCH("combine", hipLaunchKernelGGL((k_combine_low<DIM, LT>), grid, block, 0, s,
                                             G, A));
@@ -3327,50 +3475,42 @@ void stage_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A,
     NS_LAUNCH("lim2", hipLaunchKernelGGL((k_lim2<DIM, 2, SEV, LT>), grid, block, 0, s, G, A,
                                          gas));
   } else {
-    // the work lists hold a small fraction of the edges (~1.5% of them in the
-    // 3D shock tube); up to 4M lanes cover a list without striding, and
-    // blocks past its end exit at once
-    const dim3 rgrid(std::min<unsigned>(grid.x, 16384u));
-    bool merged = false;
-    if constexpr (DIM == 3) {
-      if (passes != 1) {
-        merged = true;
+    auto first = [&](auto keep) {
+      constexpr bool KEEP = decltype(keep)::value;
+      if (G.byrow)
+        NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first_rows<DIM, SEV, KEEP, LT>), grid,
+                                                  block, 0, s, G, A, gas));
+      else
+        NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, KEEP, LT>), lgrid,
+                                                  block, 0, s, G, A, gas));
+    };
+    auto two_passes = [&](auto keep) {
+      constexpr bool KEEP = decltype(keep)::value;
+      first(keep);
+      if constexpr (DIM == 3) {
         const dim3 egrid(spec_slices(G.nsrow) + grid.x);
-        if (A.keep) {
-          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, true, LT>), lgrid,
-                                                    block, 0, s, G, A, gas));
-          NS_LAUNCH("lim_entries", hipLaunchKernelGGL((k_lim_entries<SEV, true, LT>), egrid,
-                                                      block, 0, s, G, A, gas));
-        } else {
-          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, false, LT>), lgrid,
-                                                    block, 0, s, G, A, gas));
-          NS_LAUNCH("lim_entries", hipLaunchKernelGGL((k_lim_entries<SEV, false, LT>), egrid,
-                                                      block, 0, s, G, A, gas));
-        }
+        NS_LAUNCH("lim_entries", hipLaunchKernelGGL((k_lim_entries<SEV, KEEP, LT>), egrid, block,
+                                                    0, s, G, A, gas));
         NS_LAUNCH("fin", hipLaunchKernelGGL(k_fin_entries<LT>, egrid, block, 0, s, G, A));
-      }
-    }
-    if constexpr (DIM == 2) {
-      if (passes != 1) {
-        merged = true;
-        const dim3 wide(kWide), rows(spec_groups(G.nsrow) + lim_groups(G.N));
-        if (A.keep) {
-          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, true, LT>), lgrid,
-                                                    block, 0, s, G, A, gas));
+      } else {
+        const dim3 wide(kWide), rows(spec_groups(G) + lim_groups(G.N));
+        if (G.byrow)
+          NS_LAUNCH("lim_done", hipLaunchKernelGGL(k_lim_done_rows<LT>, grid, block, 0, s, G, A));
+        else
           NS_LAUNCH("lim_done", hipLaunchKernelGGL(k_lim_done<LT>, grid, block, 0, s, G, A));
-          NS_LAUNCH("lim_rows", hipLaunchKernelGGL((k_lim_rows<SEV, true, LT>), rows, wide, 0,
-                                                   s, G, A, gas));
-        } else {
-          NS_LAUNCH("lim_first", hipLaunchKernelGGL((k_lim_first<DIM, SEV, false, LT>), lgrid,
-                                                    block, 0, s, G, A, gas));
-          NS_LAUNCH("lim_done", hipLaunchKernelGGL(k_lim_done<LT>, grid, block, 0, s, G, A));
-          NS_LAUNCH("lim_rows", hipLaunchKernelGGL((k_lim_rows<SEV, false, LT>), rows, wide, 0,
-                                                   s, G, A, gas));
-        }
+        NS_LAUNCH("lim_rows", hipLaunchKernelGGL((k_lim_rows<SEV, KEEP, LT>), rows, wide, 0, s,
+                                                 G, A, gas));
         NS_LAUNCH("fin", hipLaunchKernelGGL(k_fin_rows<LT>, rows, wide, 0, s, G, A));
       }
-    }
-    if (!merged) {  // one pass
+    };
+    if (passes != 1) {
+      if (A.keep) two_passes(std::true_type{});
+      else two_passes(std::false_type{});
+    } else {
+      // the work list holds a small fraction of the edges (~1.5% of them in the
+      // 3D shock tube); up to 4M lanes cover a list without striding, and
+      // blocks past its end exit at once
+      const dim3 rgrid(std::min<unsigned>(grid.x, 16384u));
       NS_LAUNCH("lim1", hipLaunchKernelGGL((k_lim1<DIM, SEV, LT>), grid, block, 0, s, G, A,
                                            gas));
       NS_LAUNCH("root1", hipLaunchKernelGGL((k_root<DIM, SEV, LT>), rgrid, block, 0, s, G,
@@ -3393,8 +3533,12 @@ void dt_impl(const Gas &gas, const DevGraphT<LT> &G, const StageArgsT<LT> &A, do
                      (int *)nullptr);
   after(prof);
   before(prof, "visc_dt");
-  hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), lgrid, block, 0, s, G, A.U, A.aux, A.d,
-                     A.alpha, gas);
+  if (G.byrow)
+    hipLaunchKernelGGL((k_visc_rows<DIM, 2, SEV, LT>), grid, block, 0, s, G, A.U, A.aux, A.d,
+                       A.alpha, gas);
+  else
+    hipLaunchKernelGGL((k_visc<DIM, 2, SEV, LT>), lgrid, block, 0, s, G, A.U, A.aux, A.d,
+                       A.alpha, gas);
   after(prof);
   before(prof, "dt_partial");
   hipLaunchKernelGGL((k_dt_partial<DIM, LT>), grid, block, 0, s, G, A.d, A.partial);

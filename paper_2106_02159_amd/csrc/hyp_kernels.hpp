@@ -69,7 +69,25 @@ struct DevGraphT {
   const uint8_t *spec;
   const int32_t *srow;
   int nsrow;
+  // the listed rows are many (many_listed): every row goes by itself
+  int byrow;
 };
+
+// Are the listed rows so many that every row is better done by itself, a lane each
+// with a gather per slot (k_visc_rows and so on; the 3D limiter by entries as
+// ever)?  Beside the line path a listed row has a lane for each of its lines: that
+// hides the latency of a few rows, but loads and forms the row's own data in
+// each.  By rows, an entry that none of a wave's rows has is left out.  Step by
+// lines / by rows in ms (ten percent of the rows rough): 10000 x 2 nodes 0.19 /
+// 0.19, 30000 x 2 0.27 / 0.20, 400000 x 2 1.91 / 0.69, 500 x 400 x 2 2.60 / 1.38; by
+// the share of listed rows: 100000 x 3 x 3 periodic (89%) 5.18 / 2.60, 300 x 300 x
+// 4 (51%) 1.68 / 1.31, 300 x 300 x 6 (34%) 2.50 / 2.23, 100000 x 8 periodic (25%)
+// 0.97 / 0.78, 20 x 20 x 3000 (19%) 6.48 / 6.42 and with one pass 4.16 / 4.28,
+// 96^3 (6%) 3.04 / 3.51.
+constexpr int kManyListed = 25000;
+__host__ __device__ constexpr int many_listed(int64_t nsrow, int64_t N) {
+  return nsrow >= kManyListed && 4 * nsrow >= N;
+}
 
 template <typename LT>
 struct StageArgsT {

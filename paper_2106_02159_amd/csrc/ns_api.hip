@@ -221,14 +221,14 @@ struct ns_solver {
     ns::DevGraph g;
     g.N = N; g.W = W; g.geo = geo; g.seg = seg;
     g.mi = mi; g.rmi = rmi; g.lfac = lfac; g.crm = crm; g.rrel = rrel; g.wall = wall;
-    g.spec = spec; g.srow = srow; g.nsrow = nsrow;
+    g.spec = spec; g.srow = srow; g.nsrow = nsrow; g.byrow = ns::many_listed(nsrow, N);
     return g;
   }
   ns::DevGraphT<float> devgraph32() const {
     ns::DevGraphT<float> g;
     g.N = N; g.W = W; g.geo = geo; g.seg = seg;
     g.mi = mi; g.rmi = rmi; g.lfac = lfac; g.crm = crm; g.rrel = rrel; g.wall = wall;
-    g.spec = spec; g.srow = srow; g.nsrow = nsrow;
+    g.spec = spec; g.srow = srow; g.nsrow = nsrow; g.byrow = ns::many_listed(nsrow, N);
     return g;
   }
   ns::StageArgsT<float> args32(int in, int out, double sa, double sb, int check) const {
