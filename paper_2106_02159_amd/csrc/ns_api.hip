@@ -128,6 +128,8 @@ struct ns_solver {
   // one allocation that alloc() hands out piece by piece (see create_impl)
   char *slab = nullptr;
   size_t slab_size = 0, slab_used = 0;
+  struct Piece { void *p; size_t room; bool used; };
+  std::vector<Piece> pieces;  // of the slab, as they were cut
   int64_t bytes = 0;
   // graph on the device: one box geometry per mesh (the kernels derive the
   // column indices, m_ij and c_ij from it) and the per-node data
@@ -272,8 +274,15 @@ struct ns_solver {
     void *q = nullptr;
     const size_t n = count * sizeof(T) > 0 ? count * sizeof(T) : 1;
     const size_t step = (n + kPiece - 1) / kPiece * kPiece;
-    if (step <= slab_size - slab_used) {
+    auto best = pieces.end();  // the smallest free piece that has room
+    for (auto it = pieces.begin(); it != pieces.end(); ++it)
+      if (!it->used && it->room >= n && (best == pieces.end() || it->room < best->room)) best = it;
+    if (best != pieces.end()) {
+      q = best->p;
+      best->used = true;
+    } else if (step <= slab_size - slab_used) {
       q = slab + slab_used;
+      pieces.push_back({q, step, true});
       slab_used += step;
     } else {
       const hipError_t e = hipMallocAsync(&q, n, stream);
@@ -285,10 +294,15 @@ struct ns_solver {
     return hipSuccess;
   }
   static constexpr size_t kPiece = 512;  // alignment of the slab's pieces
-  // frees one allocation made by alloc (stream-ordered); a piece of the slab
-  // stays until the solver is destroyed
+  // frees one allocation made by alloc (stream-ordered); a piece of the slab is
+  // there for a later alloc
   template <typename T> void free_one(T *&p, size_t count) {
     if (!p) return;
+    for (Piece &piece : pieces)
+      if (piece.p == (void *)p && piece.used) {
+        piece.used = false;
+        bytes -= (int64_t)(count * sizeof(T));
+      }
     auto it = std::find(allocs.begin(), allocs.end(), (void *)p);
     if (it != allocs.end()) {
       allocs.erase(it);
@@ -404,6 +418,7 @@ void release(ns_solver *s) {
   if (s->slab) (void)hipFreeAsync(s->slab, s->stream);
   s->slab = nullptr;
   s->slab_size = s->slab_used = 0;
+  s->pieces.clear();
 
   for (hipGraphExec_t &g : s->step_graph) {
     if (g) (void)hipGraphExecDestroy(g);
