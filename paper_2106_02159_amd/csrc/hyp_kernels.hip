@@ -1615,57 +1615,29 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
   } else if constexpr (MODE == 1 || MODE == 2) {
     finish<DIM>(G, A, i, u1);
   } else {
+    static_assert(CACHE);
     store_state<NC>(A.U1, N, i, u1);
     const Bounds b = load_bounds(A, N, i);
     LT *__restrict__ lt2 = A.lt2;
     uint32_t slow = 0;
     uint32_t nzm = 0;  // slots whose stored product may be nonzero (fin_row)
-    if constexpr (!CACHE) {
-      // reload the neighbour data rather than keep a whole row of it live
-      asm volatile("" ::: "memory");
-    }
 #pragma unroll
     for (int ch = 0; ch < C::NCH; ++ch) {
-      if constexpr (!CACHE) colk.fence();
       double P[C::CH][NC], l[C::CH];
       int32_t jc[C::CH];
-      if constexpr (CACHE) {
 #pragma unroll
-        for (int kk = 0; kk < C::CH; ++kk) {
-          const int k = ch * C::CH + kk;
-          const int o = k < C::W / 2 ? k : k - 1;
-          if (k != C::W / 2 && o < NLDS) {
+      for (int kk = 0; kk < C::CH; ++kk) {
+        const int k = ch * C::CH + kk;
+        const int o = k < C::W / 2 ? k : k - 1;
+        if (k != C::W / 2 && o < NLDS) {
 #pragma unroll
-            for (int q = 0; q < NC; ++q) P[kk][q] = Ps[o < NLDS ? o : 0][q][lane];
-          } else {
+          for (int q = 0; q < NC; ++q) P[kk][q] = Ps[o < NLDS ? o : 0][q][lane];
+        } else {
 #pragma unroll
-            for (int q = 0; q < NC; ++q) P[kk][q] = Pc[k][q];
-          }
-          l[kk] = lc[k];
-          jc[kk] = colk[k];
+          for (int q = 0; q < NC; ++q) P[kk][q] = Pc[k][q];
         }
-      } else {
-        // one chunk of gathers in flight at a time (bounds the registers)
-        asm volatile("" ::: "memory");
-        PIn<DIM> x[C::CH];
-        double la[C::CH], lb[C::CH];
-#pragma unroll
-        for (int kk = 0; kk < C::CH; ++kk) {
-          const int k = ch * C::CH + kk;
-          const int64_t e = eidx<DIM>(k, i);
-          jc[kk] = colk[k];
-          if (k == C::W / 2) continue;  // the diagonal has no P
-          const int64_t js = jc[kk] >= 0 ? jc[kk] : i;
-          gather_P<DIM>(G, A, e, js, colk.mass(k), x[kk]);
-          la[kk] = lt1[e];
-          lb[kk] = lt1[eidx<DIM>(tslot<DIM>(k), js)];
-        }
-#pragma unroll
-        for (int kk = 0; kk < C::CH; ++kk) {
-          if (ch * C::CH + kk == C::W / 2) continue;
-          make_P<DIM>(R, x[kk], P[kk]);
-          l[kk] = fmin(la[kk], lb[kk]);
-        }
+        l[kk] = lc[k];
+        jc[kk] = colk[k];
       }
 #pragma unroll
       for (int kk = 0; kk < C::CH; ++kk) {
@@ -1686,9 +1658,9 @@ __device__ __forceinline__ void lim2_row(const DevGraphT<LT> &G, const StageArgs
         if (sv != LT(0) || ((slow >> k) & 1u)) nzm |= 1u << k;
       }
     }
-    if constexpr (DIM == 2) A.nzm[i] = nzm;
+    A.nzm[i] = nzm;
     if (slow) {
-      uint32_t *__restrict__ q2 = A.q2 ? A.q2 : A.q;
+      uint32_t *__restrict__ q2 = A.q2;
       uint32_t t = atomicAdd(&A.qcnt[1], (uint32_t)__builtin_popcount(slow));
       while (slow) {
         const int k = __builtin_ctz(slow);
@@ -2792,7 +2764,7 @@ __device__ __forceinline__ void lim2b_row(const DevGraphT<LT> &G, const StageArg
     }
   }
   if (slow) {
-    uint32_t *__restrict__ q2 = A.q2 ? A.q2 : A.q;
+    uint32_t *__restrict__ q2 = A.q2;
     uint32_t t = atomicAdd(&A.qcnt[1], (uint32_t)__builtin_popcount(slow));
     while (slow) {
       const int k = __builtin_ctz(slow);
@@ -2820,7 +2792,7 @@ __device__ __forceinline__ void root_range(const DevGraphT<LT> &G, const StageAr
   constexpr int NC = DIM + 2;
   const int64_t N = G.N;
   const uint32_t n = A.qcnt[PASS - 1];
-  const uint32_t *__restrict__ q = PASS == 2 && A.q2 ? A.q2 : A.q;
+  const uint32_t *__restrict__ q = PASS == 2 ? A.q2 : A.q;
   LT *__restrict__ lt = PASS == 1 ? A.lt1 : A.lt2;
   for (uint32_t t = start; t < n; t += stride) {
     const int64_t e = q[t];

@@ -122,8 +122,8 @@ struct StageArgsT {
   // qcnt[p] counts the entries of pass p+1 (reset by k_lo).
   uint32_t *q;
   uint32_t *qcnt;
-  // the pass-2 work list q2 (W*Np entries; null: q, filled after q is emptied).
-  // Launched two-pass limiting lists no roots: 2D lists the limited rows in q
+  // the pass-2 work list q2 (W*Np entries; the persistent steps': q again, emptied
+  // before).  Launched two-pass limiting lists no roots: 2D lists the limited rows in q
   // (row_lists.hpp), with the lists' lengths and root counts in q2, 3D its spread
   // root counters in q2
   uint32_t *q2 = nullptr;

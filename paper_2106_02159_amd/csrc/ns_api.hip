@@ -174,8 +174,8 @@ struct ns_solver {
          *U1 = nullptr, *partial = nullptr, *tau = nullptr;
   int *flags = nullptr;
   uint32_t *q = nullptr, *qcnt = nullptr;
-  uint32_t *nzm = nullptr;  // 2D: slots with a pass-2 weight, per row
-  uint32_t *lim = nullptr;  // 2D: slots limited by the row's own search
+  uint32_t *nzm = nullptr;  // slots with a pass-2 weight, per row
+  uint32_t *lim = nullptr;  // slots limited by the row's own search
   // host copies of device scalars (pageable: no pinned allocation, whose
   // release would synchronize the whole device)
   int hflags[4] = {0, 0, 0, 0};
