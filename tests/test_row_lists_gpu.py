@@ -21,6 +21,9 @@ def state(mesh, kind):
     rough = W.random_rough_state(mesh, seed=mesh.n[0])
     if kind == "rough":
         return rough
+    if kind == "waves":  # all rows limited, alike along x
+        w = [0.3 * np.sin(2.0 * np.pi * y / (6.0 * mesh.spacing()[1]) + k) for k in range(3)]
+        return W.conserved(1.0 + w[0], (0.5 * w[1], 0.5 * w[2]), 1.0 + w[0], 1.4)
     U = W.constant_state(mesh, rho=1.0, vel=(0.3, -0.2))
     where = np.abs((x if kind == "along y" else y) - 0.5 * mesh.hi[0 if kind == "along y" else 1])
     hit = where < 0.03
@@ -47,6 +50,13 @@ def test_one_mesh(n, per, kind, precision):
         out.append((t, s.get_state()))
     assert out[0][0] == out[1][0]
     assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("precision", [abi.PREC_FP64, abi.PREC_MIXED])
+@pytest.mark.parametrize("kind", ["waves", "rough"])
+def test_many_rows(kind, precision):
+    """More limited rows than a round of 512 workgroups with 512 rows each."""
+    test_one_mesh((701, 613), (0, 0), kind, precision)
 
 
 def test_pack():
