@@ -391,17 +391,19 @@ __global__ __launch_bounds__(kParBlock) void k_mg_residual(MGLevel L, float cdt,
 // V-cycle at 501 x 400), while one CU runs an iteration in 0.3 - 1 us from
 // LDS: the levels from the first with at most kTailNodes nodes on (and whose
 // iterates fit kTailWords) go through one kernel.  The line lies where one
-// CU's iteration costs what a launch does: 4096 nodes of 9 neighbours, 2048
-// of 27.  A lane owns up to NPT nodes of a level: its right-hand side,
-// direction and diagonal stay in registers while it smooths, the two buffers
-// of the iterate are in LDS; b of the levels below goes through global memory
-// between lanes of the same number only (coarse node I is restricted and
-// smoothed by lane I mod kTailThreads).  501 x 400 (levels of 3264, 858 and 238
-// nodes): 53 us (velocity) and 46 us (energy) for 30 launches before, about
-// 120 and 180 us; most of it the arithmetic of the largest level, 3 us per
-// iteration on one CU's SIMDs.
+// CU's iteration costs what a launch does: 4096 nodes of 9 neighbours, 1024
+// of 27 (a parabolic step with no such levels / up to 1024 / 2048 / 4096 nodes:
+// 12^3 2.53 / 2.11 / 2.34 / 2.41 ms, 24^3 3.50 / 3.05 / 3.05 / 3.63, 48^3 4.99 /
+// 4.51 / 4.49 / 5.17, 101 x 67 x 83 9.15 / 8.60 / 8.92 / 9.05).  A lane owns up
+// to NPT nodes of a level: its right-hand side, direction and diagonal stay in
+// registers while it smooths, the two buffers of the iterate are in LDS; b of the
+// levels below goes through global memory between lanes of the same number only
+// (coarse node I is restricted and smoothed by lane I mod kTailThreads).  501 x 400
+// (levels of 3264, 858 and 238 nodes): 53 us (velocity) and 46 us (energy) for
+// 30 launches before, about 120 and 180 us; most of it the arithmetic of the
+// largest level, 3 us per iteration on one CU's SIMDs.
 constexpr int kTailThreads = 1024, kTailWords = 24576;
-template <int DIM> constexpr int kTailPer = DIM == 2 ? 4 : 2;  // nodes of a lane
+template <int DIM> constexpr int kTailPer = DIM == 2 ? 4 : 1;  // nodes of a lane
 template <int DIM> constexpr int kTailNodes = kTailPer<DIM> * kTailThreads;
 constexpr int kTailLevels = 16;
 struct MGTail {

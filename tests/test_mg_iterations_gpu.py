@@ -16,6 +16,8 @@ CASES = [((33, 33), (0, 0), (7, 7, 16, 18)), ((64, 64), (0, 0), (8, 7, 16, 17)),
          ((1366, 3), (0, 0), (9, 101, 10, 216)), ((500, 9), (1, 0), (9, 22, 11, 42)),
          ((12, 12, 12), (0, 0, 0), (6, 6, 8, 10)), ((16, 8, 16), (1, 0, 1), (7, 7, 9, 11)),
          ((25, 5, 16), (0, 0, 0), (7, 7, 9, 14)), ((26, 5, 16), (0, 0, 0), (7, 7, 9, 14)),
+         ((16, 8, 8), (0, 0, 0), (7, 6, 8, 10)), ((15, 9, 8), (0, 0, 0), (7, 6, 8, 11)),
+         ((8, 16, 8), (1, 0, 1), (7, 7, 12, 11)), ((10, 11, 10), (0, 1, 0), (6, 6, 9, 9)),
          ((24, 24, 24), (0, 0, 0), (7, 7, 9, 9)), ((24, 24, 24), (1, 1, 1), (7, 7, 12, 11)),
          ((31, 17, 45), (0, 1, 0), (8, 7, 12, 13)), ((48, 48, 48), (0, 0, 0), (8, 7, 10, 11))]
 
