@@ -409,8 +409,8 @@ struct ViscRow {
 
 // Adds the entries of line l to the indicator's sums and stores d_ij for
 // j > i.  ANY: the row may be interior (its coefficients are then the
-// table's).
-template <int DIM, int IND, int SEV, bool ANY, typename LT>
+// table's).  SKIP: leave out an entry that none of the wave's rows has.
+template <int DIM, int IND, int SEV, bool ANY, bool SKIP, typename LT>
 __device__ __forceinline__ void visc_line(const DevGraphT<LT> &G,
                                           const double *__restrict__ U,
                                           const double *__restrict__ aux,
@@ -426,7 +426,7 @@ __device__ __forceinline__ void visc_line(const DevGraphT<LT> &G,
   for (int t = 0; t < 3; ++t) {
     const int k = 3 * l + t;
     const int32_t j = jv[k];
-    if (ANY && !__any(j >= 0)) continue;  // (absent entries add zeros)
+    if (SKIP && !__any(j >= 0)) continue;  // (absent entries add zeros)
     const int64_t js = j >= 0 ? j : i;
     double uj[NC];
     load_state<NC>(U, N, js, uj);
@@ -498,7 +498,7 @@ __device__ __forceinline__ void visc_spec(const DevGraphT<LT> &G,
   const SpecLane<DIM> L(G);
   const ViscRow<DIM, IND> R(G, U, aux, g, L.i);
   double num = 0.0, den = 0.0, scl = 0.0;
-  visc_line<DIM, IND, SEV, false, LT>(G, U, aux, d, g, row_nbr<DIM>(G, L.i), L.i, R, L.line,
+  visc_line<DIM, IND, SEV, false, false, LT>(G, U, aux, d, g, row_nbr<DIM>(G, L.i), L.i, R, L.line,
                                       L.ok, num, den, scl);
   num = L.sum(num);
   den = L.sum(den);
@@ -508,7 +508,7 @@ __device__ __forceinline__ void visc_spec(const DevGraphT<LT> &G,
 
 // Any row by one lane: sums along the row as the line sweep forms them if it is
 // interior, line by line as visc_spec if not.
-template <int DIM, int IND, int SEV, typename LT>
+template <int DIM, int IND, int SEV, bool SKIP, typename LT>
 __device__ __forceinline__ void visc_row(const DevGraphT<LT> &G,
                                          const double *__restrict__ U,
                                          const double *__restrict__ aux,
@@ -520,7 +520,7 @@ __device__ __forceinline__ void visc_row(const DevGraphT<LT> &G,
   double num = 0.0, den = 0.0, scl = 0.0, tn = 0.0, td = 0.0, ts = 0.0;
 #pragma unroll 1
   for (int l = 0; l < Cfg<DIM>::W / 3; ++l) {
-    visc_line<DIM, IND, SEV, true, LT>(G, U, aux, d, g, jv, i, R, l, store, num, den, scl);
+    visc_line<DIM, IND, SEV, true, SKIP, LT>(G, U, aux, d, g, jv, i, R, l, store, num, den, scl);
     if (!in) {
       tn += num; td += den; ts += scl;
       num = den = scl = 0.0;
@@ -831,7 +831,7 @@ __global__ __launch_bounds__(kBlock) void k_visc_rows(DevGraphT<LT> G,
                                                       LT *__restrict__ d,
                                                       LT *__restrict__ alpha, Gas g) {
   const OwnRow<DIM> r(G);
-  visc_row<DIM, IND, SEV, LT>(G, U, aux, d, alpha, g, r.nb, r.i, r.ok);
+  visc_row<DIM, IND, SEV, true, LT>(G, U, aux, d, alpha, g, r.nb, r.i, r.ok);
 }
 
 // ---------------------------------------------------------------------------
@@ -1004,7 +1004,7 @@ __device__ __forceinline__ void clear_counters(const StageArgsT<LT> &A) {
 
 // The general path (see visc_line): adds the entries of line l of row i;
 // csum is the sum of c_ij, the diagonal entry's flux goes to F^H directly.
-template <int DIM, bool ANY, typename LT>
+template <int DIM, bool ANY, bool SKIP, typename LT>
 __device__ __forceinline__ void lo_line(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                         const Gas &g, const BoxNbr<DIM> &jv, int64_t i,
                                         const double *ui, const double *vi, double pi,
@@ -1012,7 +1012,7 @@ __device__ __forceinline__ void lo_line(const DevGraphT<LT> &G, const StageArgsT
 #pragma clang fp contract(off)  // the same bits in every kernel
   constexpr int NC = DIM + 2, ALL = (1 << DIM) - 1, C = Cfg<DIM>::W / 2;
   const int64_t N = G.N;
-  if (ANY) {  // (absent entries add zeros)
+  if (SKIP) {  // (absent entries add zeros)
     const bool any = jv[3 * l] >= 0 || jv[3 * l + 1] >= 0 || jv[3 * l + 2] >= 0;
     if (!__any(any)) return;
   }
@@ -1091,7 +1091,7 @@ __device__ __forceinline__ void lo_spec(const DevGraphT<LT> &G, const StageArgsT
   lo_clear(S, ui[0], A.aux[Aux<DIM>::PHI * G.N + i]);
 #pragma unroll
   for (int q = 0; q < DIM; ++q) csum[q] = 0.0;
-  lo_line<DIM, false>(G, A, g, row_nbr<DIM>(G, i), i, ui, vi, pi, (double)al, L.line, S, csum);
+  lo_line<DIM, false, false>(G, A, g, row_nbr<DIM>(G, i), i, ui, vi, pi, (double)al, L.line, S, csum);
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
     S.acc[q] = L.sum(S.acc[q]);
@@ -1111,7 +1111,7 @@ __device__ __forceinline__ void lo_spec(const DevGraphT<LT> &G, const StageArgsT
 }
 
 // A row by one lane (see visc_row).
-template <int DIM, typename LT>
+template <int DIM, bool SKIP, typename LT>
 __device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<LT> &A,
                                        const Gas &g, BoxNbr<DIM> jv, int64_t i,
                                        bool store = true) {
@@ -1129,7 +1129,7 @@ __device__ __forceinline__ void lo_row(const DevGraphT<LT> &G, const StageArgsT<
   for (int q = 0; q < DIM; ++q) csum[q] = tc[q] = 0.0;
 #pragma unroll 1
   for (int l = 0; l < Cfg<DIM>::W / 3; ++l) {
-    lo_line<DIM, true>(G, A, g, jv, i, ui, vi, pi, (double)al, l, S, csum);
+    lo_line<DIM, true, SKIP>(G, A, g, jv, i, ui, vi, pi, (double)al, l, S, csum);
     if (!in) {
 #pragma unroll
       for (int q = 0; q < NC; ++q) {
@@ -1159,7 +1159,7 @@ template <int DIM, typename LT>
 __global__ __launch_bounds__(kBlock) void k_lo_rows(DevGraphT<LT> G, StageArgsT<LT> A, Gas g) {
   clear_counters<DIM>(A);
   const OwnRow<DIM> r(G);
-  lo_row<DIM>(G, A, g, r.nb, r.i, r.ok);
+  lo_row<DIM, true>(G, A, g, r.nb, r.i, r.ok);
 }
 
 // The interior rows of row block blk, line by line (line_sweep.hpp).
@@ -1689,20 +1689,27 @@ __global__ __launch_bounds__(kBlock) void k_lim2(DevGraphT<LT> G, StageArgsT<LT>
 //   k_lim_rows    runs both limiter passes, roots included, for the marked
 //                 rows, 8 lanes (the 8 pairs) to a row;
 //   k_fin_rows    adds the pass-2 part of those that have one, 8 lanes to a
-//                 row again.
+//                 row again, or a lane to each of 64 neighbouring rows.
 // Marked rows come in long runs, so the waves of k_lim_rows and k_fin_rows take
 // equal parts of the list; a wave that worked through its own slice of 64 rows
 // had up to 8 rounds of 8 rows, 13 us each, and workgroups with fixed slices all
 // over the mesh lined up with fronts.
 // Against one sweep that gathered every neighbour slot by slot, kept P for
 // pass 2, and listed the entries with a root for two further kernels (FP64,
-// limiter and final update of a stage): 2.61 -> 1.48 ms at 4096^2, 0.27 ->
-// 0.13 ms at 1001 x 1003, 0.11 -> 0.06 ms at 256^2; there the appends to the
+// limiter and final update of a stage): 2.60 -> 1.33 ms at 4096^2, 0.29 ->
+// 0.13 ms at 1001 x 1003, 0.15 -> 0.05 ms at 256^2; there the appends to the
 // lists, serial at their counters (15 ns each), and one lane's row of 8
 // searches took the time.  k_lim_first is bound by the latency of its line
-// loads at 4 waves per SIMD (0.80 ms at 4096^2, 245 B per node: 5.1 TB/s),
+// loads at 4 waves per SIMD (0.82 ms at 4096^2, 245 B per node: 5.0 TB/s),
 // k_lim_done by memory bandwidth (0.27 ms), k_lim_rows by the root finder's
-// dependent chain.
+// dependent chain and, where most rows are limited, by its 660 vector
+// instructions for 8 rows.  The whole step by the share of rows with jumps
+// everywhere (2048^2, one sweep / now): 1% 4.27 / 2.97 ms, 10% 4.45 / 3.21, 50%
+// 6.17 / 4.38, 100% 8.38 / 5.40.  The one sweep was ahead only where every row of a
+// large mesh is limited and rows are alike along x, so that its lanes never
+// diverged: waves along y of 6 nodes, 1500^2, 2.98 / 3.56 ms, of 12 nodes 2.78 /
+// 3.05; along x of 6 nodes 5.77 / 5.20.  (A lane per row here, pair by pair, takes
+// 3.0 ms for the former's k_lim_rows, not 1.85.)
 // Both searches of a pair are evaluated where a row needs them, on operands
 // in the order the other row uses, so that both rows obtain the same l_ij
 // (as for every kernel here, without fused multiply-adds of the compiler's
@@ -2397,13 +2404,13 @@ __global__ __launch_bounds__(kWide) void k_fin_rows(DevGraphT<LT> G, StageArgsT<
 // rows without a pass-2 part are finished.  k_fin_entries adds that part of
 // the others the same way.  Against three sweeps over all entries that
 // gathered slot by slot, two root kernels and a final sweep (FP64, limiter and
-// final update of a stage): 6.47 -> 3.67 ms at 192^3, 1.99 -> 1.02 ms at 128^3,
-// and 0.55 -> 0.26 ms at 101 x 67 x 83 with FP32 coefficients.  k_lim_first
-// (1.18 ms at 192^3) is bound by arithmetic and load latency at 3 waves per
-// SIMD (held to 4 it spills: 1.68 ms).  k_lim_entries (1.67 ms) spends 0.42 ms
-// in the root finder, the rest on each group's chain of gathers; so does
-// k_fin_entries (0.80 ms).  3 waves per SIMD, since at 4 the former spills
-// (1.75 ms).
+// final update of a stage): 6.48 -> 3.95 ms at 192^3, 2.01 -> 1.13 ms at 128^3,
+// and 0.56 -> 0.27 ms at 101 x 67 x 83 with FP32 coefficients.  k_lim_first
+// (1.25 ms at 192^3) is bound by arithmetic and load latency at 3 waves per
+// SIMD (held to 4 it spills: 1.4 times the time).  k_lim_entries (1.88 ms) spends
+// a quarter of it in the root finder, the rest on each group's chain of gathers; so
+// does k_fin_entries (0.82 ms).  3 waves per SIMD, since at 4 the former spills and
+// is slower by 2%.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -3414,7 +3421,7 @@ __global__ __launch_bounds__(kBlock) void k_persist(DevGraphT<LT> G, PersistArgs
       case PP_PRIM: prim_row<DIM>(G.N, A.U, A.aux, g, i); break;
       case PP_VISC:
         if (i < G.N)
-          visc_row<DIM, 0, SEV, LT>(G, A.U, A.aux, A.d, A.alpha, g, block_nbr<DIM>(G, blk, i), i);
+          visc_row<DIM, 0, SEV, false, LT>(G, A.U, A.aux, A.d, A.alpha, g, block_nbr<DIM>(G, blk, i), i);
         break;
       case PP_DTP: dt_partial_blk<DIM, LT>(G, A.d, A.partial, blk, i); break;
       case PP_DTF:
@@ -3422,7 +3429,7 @@ __global__ __launch_bounds__(kBlock) void k_persist(DevGraphT<LT> G, PersistArgs
         break;
       case PP_LO:
         clear_lists(A, r == 0 && tid == 0);
-        if (i < G.N) lo_row<DIM>(G, A, g, block_nbr<DIM>(G, blk, i), i);
+        if (i < G.N) lo_row<DIM, false>(G, A, g, block_nbr<DIM>(G, blk, i), i);
         break;
       case PP_LIM1: lim1_row<DIM, SEV, LT>(G, A, g, blk, i); break;
       case PP_ROOT1: root_range<DIM, 1, SEV, LT>(G, A, g, r * kBlock + tid, nr * kBlock); break;

@@ -6,10 +6,11 @@
 // node i at c*N + i); edge arrays are sliced ELL (rows in slices of 64, slot-major
 // within a slice: slot k of row i at ((i/64) W + k) 64 + i%64), so lane i of
 // a wavefront reading slot k of its row produces one coalesced access.  One
-// lane owns one row; the viscosity and low-order sweeps read the neighbours
-// along stencil lines (line_sweep.hpp), as the 2D limiter does; the other
-// limiter sweeps gather them through the L1/L2 caches.  Sweeps, in dependency order (each needs the
-// previous one complete over the whole mesh):
+// lane owns one row; the viscosity, the low-order and the first limiter sweep
+// read the neighbours along stencil lines (line_sweep.hpp; thin meshes and the
+// persistent steps slot by slot), the other limiter sweeps gather them through
+// the L1/L2 caches.  Sweeps, in dependency order (each needs the previous one
+// complete over the whole mesh):
 //   k_prim   per node: sound speed a, a p^(-(g-1)/(2g)), eta, Phi
 //   k_visc   d^L_ij for j > i (Sec. 3.1), written to (i,j) and (j,i);
 //            indicator alpha_i (Sec. 3.2)

@@ -15,11 +15,12 @@
 //
 // All other rows (a few in a thousand on a large 2D mesh, 3% at 192^3) are
 // listed once per solver; workgroups at the front of the same launch run them
-// through the general per-slot path, one lane per row and line.
+// through the general per-slot path, one lane per row and line.  (Meshes a few
+// nodes thick, mostly such rows, take every row by itself: many_listed.)
 //
 // Per launch, gather per slot -> along lines (FP64): graph viscosity 0.81 ->
-// 0.55 ms at 4096^2, 1.06 -> 0.78 ms at 192^3; low-order sweep 1.09 -> 0.72
-// and 1.36 -> 0.93 ms.  VALU instructions per row fall from 1176 to 790 and
+// 0.54 ms at 4096^2, 1.06 -> 0.79 ms at 192^3; low-order sweep 1.09 -> 0.73
+// and 1.37 -> 0.95 ms.  VALU instructions per row fall from 1176 to 790 and
 // from 1059 to 770 in 2D.
 #pragma once
 
